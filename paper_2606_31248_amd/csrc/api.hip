@@ -64,6 +64,8 @@ static strata_status check_desc(const strata_na3d_desc* d) {
   REQUIRE(n * d->head_dim < kMaxElems, "desc: tensor too large");
   if (d->head_dim != 32 && d->head_dim != 64 && d->head_dim != 128)
     return set_error(STRATA_ERR_UNSUPPORTED, "head_dim %d not supported (32, 64 or 128)", d->head_dim);
+  // grids that no device holds: the kernels index a tile's tokens with 32 bits
+  if (!na3d_any_takes(*d)) return set_error(STRATA_ERR_UNSUPPORTED, "desc: grid too large for 32-bit token indices");
   return STRATA_OK;
 }
 
@@ -115,7 +117,7 @@ static void launch_fwd(const strata_na3d_desc& d, const NaOpts& o, const void* q
   if (!launch_na3d_fwd_col(d, o, q, k, v, out, lse, s) && !launch_na3d_fwd_zs(d, o, q, k, v, cs, out, lse, s) &&
       !launch_na3d_fwd_lsg(d, o, q, k, v, cs, out, lse, s) && !launch_na3d_fwd_mfma(d, o, q, k, v, cs, out, lse, s) &&
       !launch_na3d_fwd_d128(d, o, q, k, v, cs, out, lse, s))
-    launch_na3d_fwd_ref(d, o, q, k, v, cs, out, lse, s);
+    launch_na3d_fwd_any(d, o, q, k, v, cs, out, lse, s);
 }
 
 static strata_status na3d_fwd_impl(const strata_na3d_desc* desc, const strata_na3d_opts* opts,
@@ -200,7 +202,7 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
     ga = ws + L.da_hi;
     bo.dout_lo = lo;
   } else if (!fuse_d) {
-    launch_na3d_bwd_ref(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);
+    launch_na3d_bwd_any(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);
   }
   if (launch_na3d_bwd_col(*desc, bo, q, k, v, ga, lse, dvec, dq, dk, dv, s))
     return check_launch(opts ? "strata_na3d_bwd_ex" : "strata_na3d_bwd");
@@ -210,14 +212,14 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   int* emax = na3d_bwd_dkdv_kvp_takes(*desc, bo) ? reinterpret_cast<int*>(ws + L.emax) : nullptr;
   if (!launch_na3d_bwd_dq_mfma(*desc, bo, q, k, v, cs, ga, lse, dvec, fuse_d ? out : nullptr, emax, dq, s)) {
     emax = nullptr;
-    if (fuse_d) launch_na3d_bwd_ref(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);
+    if (fuse_d) launch_na3d_bwd_any(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);
     if (!launch_na3d_bwd_dq_d128(*desc, bo, q, k, v, cs, ga, lse, dvec, dq, s))
-      launch_na3d_bwd_ref(1, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);
+      launch_na3d_bwd_any(1, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);
   }
   if (!launch_na3d_bwd_dkdv_kvp(*desc, bo, q, k, v, cs, ga, lse, dvec, emax, dk, dv, s) &&
       !launch_na3d_bwd_dkdv_mfma(*desc, bo, q, k, v, cs, ga, lse, dvec, dk, dv, s) &&
       !launch_na3d_bwd_dkdv_d128(*desc, bo, q, k, v, cs, ga, lse, dvec, dk, dv, s))
-    launch_na3d_bwd_ref(2, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);
+    launch_na3d_bwd_any(2, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);
   return check_launch(opts ? "strata_na3d_bwd_ex" : "strata_na3d_bwd");
 }
 

@@ -34,8 +34,10 @@ void launch_rope_phases(const float* coords, int B, int H, int W, int head_dim, 
 void launch_rope_apply(const void* x, void* y, const float* cs, int B, int heads, int Z, int H,
                        int W, int head_dim, strata_dtype dt, int transpose, hipStream_t s);
 
-// Plain per-query forward (float32 arithmetic), any supported dtype / head_dim.
-void launch_na3d_fwd_ref(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k,
+// Any supported dtype, head_dim, window and grid, in float32 arithmetic on the
+// float32 matrix instructions; na3d_any_takes: every grid that a device can hold.
+bool na3d_any_takes(const strata_na3d_desc& d);
+void launch_na3d_fwd_any(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k,
                          const void* v, const float* cs, void* out, float* lse, hipStream_t s);
 
 // bf16 MFMA forward sweeping the key levels once per head (window 3x7x7, Z = 8);
@@ -81,9 +83,9 @@ struct BwdOpts {
   const void* dout_lo = nullptr;
 };
 
-// Plain backward (float32 arithmetic), one part per call: 0 = D = rowsum(dO * O)
+// Backward of any problem (float32 arithmetic), one part per call: 0 = D = rowsum(dO * O)
 // into dvec, 1 = dq, 2 = dk and dv (parts 1 and 2 read dvec).
-void launch_na3d_bwd_ref(int part, const strata_na3d_desc& d, const BwdOpts& o, const void* q,
+void launch_na3d_bwd_any(int part, const strata_na3d_desc& d, const BwdOpts& o, const void* q,
                          const void* k, const void* v, const float* cs, const void* out,
                          const void* dout, const float* lse, void* dq, void* dk, void* dv,
                          float* dvec, hipStream_t s);

@@ -1,0 +1,123 @@
+"""Host check of the tile geometry of the any-window attention kernels
+(`csrc/any_walk.h`), compiled with g++ on its own.
+
+For grids and windows of every form (odd windows, windows that span their axis
+with either parity, columns, single positions, extents that the tile does not
+divide): the tiles' live tokens cover the grid once; the chunks of every tile
+stay inside the grid and show each lane exactly the tokens of its
+border-clamped window (Sec. 3.2), or the queries whose window holds it, once
+each, by brute force over the definition; and the division by a fixed number
+is exact up to 2^30.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2606_31248_amd", "csrc")
+
+HARNESS = r"""
+#define __host__
+#define __device__
+#define __forceinline__ inline
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+using std::max;
+using std::min;
+#include "any_walk.h"
+using namespace strata::any;
+
+static int begin_of(int q, int L, int k) {  // nearest window of k positions inside [0, L)
+  int s = q - (k - 1) / 2;
+  return s < 0 ? 0 : s + k > L ? L - k : s;
+}
+static bool holds(int q, int j, int L, int k) { const int s = begin_of(q, L, k); return j >= s && j < s + k; }
+
+template <bool INV>
+static int check(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
+  const AnyDims d = any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f);
+  const int N = Z * H * W;
+  std::vector<int> cover((size_t)B * heads * N, 0);
+  for (int64_t t = 0; t < d.tiles; ++t)
+    for (int m = 0; m < 16; ++m) {
+      const Walk w = Walk::make<INV>(d, (uint32_t)t, m);
+      if (w.bh < 0 || w.bh >= (int64_t)B * heads || w.b != w.bh / heads) return printf("tile index\n"), 1;
+      if (w.z < 0 || w.z >= Z || w.y < 0 || w.y >= H || w.x < 0 || w.x >= W) return printf("token outside\n"), 1;
+      if (w.live) cover[w.bh * N + w.mine()]++;
+      if (t > 40 && t % 7) continue;  // the walk of a part of the tiles
+      std::vector<int> seen(N, 0);
+      for (uint32_t i0 = 0; i0 < w.n; i0 += 16) {
+        int bz, by, bx;
+        w.at(min(i0 + m, w.n - 1), bz, by, bx);
+        const uint32_t own = w.tok(bz, w.plane(by, bx));
+        for (int g = 0; g < 4; ++g) {
+          uint32_t tk[4];
+          bool in[4];
+          w.four(i0 + 4 * g, tk, in);
+          for (int r = 0; r < 4; ++r) {
+            if (tk[r] >= (uint32_t)N) return printf("token %u of %d\n", tk[r], N), 1;
+            if (in[r]) seen[tk[r]]++;
+            if (4 * g + r == m && tk[r] != own) return printf("row and column disagree\n"), 1;
+          }
+        }
+      }
+      for (int z = 0; z < Z; ++z)
+        for (int y = 0; y < H; ++y)
+          for (int x = 0; x < W; ++x) {
+            const bool want = INV ? holds(z, w.z, Z, kz) && holds(y, w.y, H, ky) && holds(x, w.x, W, kx)
+                                  : holds(w.z, z, Z, kz) && holds(w.y, y, H, ky) && holds(w.x, x, W, kx);
+            if (seen[(z * H + y) * W + x] != (want ? 1 : 0)) return printf("window of tile %d lane %d\n", (int)t, m), 1;
+          }
+    }
+  for (int c : cover)
+    if (c != 1) return printf("a token in %d tiles\n", c), 1;
+  return 0;
+}
+
+int main() {
+  std::mt19937 rng(7);
+  auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  for (int it = 0; it < 400; ++it) {
+    int L[3], k[3];
+    for (int a = 0; a < 3; ++a) {
+      L[a] = pick(1, a == 0 ? 20 : 24);
+      const int kind = pick(0, 4);
+      k[a] = kind == 0 ? L[a] : kind == 1 ? 1 : min(2 * pick(0, 5) + 1, L[a] - (L[a] + 1) % 2);
+      if (k[a] < 1) k[a] = 1;
+    }
+    const int B = pick(1, 2), h = pick(1, 3);
+    if (check<false>(B, h, L[0], L[1], L[2], k[0], k[1], k[2]) || check<true>(B, h, L[0], L[1], L[2], k[0], k[1], k[2])) {
+      printf("grid %dx%dx%d window %dx%dx%d\n", L[0], L[1], L[2], k[0], k[1], k[2]);
+      return 1;
+    }
+  }
+  for (int it = 0; it < 200000; ++it) {
+    const uint32_t n = it < 4096 ? it + 1 : 1 + (uint32_t)(rng() % (1u << pick(1, 30)));
+    const FastDiv f(n);
+    const uint32_t q = ((1u << 30) - 1) / n;
+    for (uint32_t i : {0u, n - 1, n, (uint32_t)(rng() >> 2), q * n - 1, q * n, (1u << 30) - 1})
+      if (i < (1u << 30) && f.div(i) != i / n) return printf("%u / %u = %u\n", i, n, f.div(i)), 1;
+  }
+  if (any_fits(1, 1, 1 << 12, 1 << 12, 1 << 12, 3, 3, 3) || !any_fits(81, 16, 24, 512, 512, 9, 9, 9)) return printf("fits\n"), 1;
+  printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_any_walk(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    src = tmp_path / "any_walk_check.cpp"
+    exe = tmp_path / "any_walk_check"
+    src.write_text(HARNESS)
+    subprocess.run([gxx, "-O2", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-I", CSRC, str(src), "-o", str(exe)],
+                   check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert out.stdout.startswith("ok")

@@ -1,0 +1,85 @@
+"""The any-window attention kernels (float32 matrix instructions) against the CPU
+oracle at the sizes where their tiling can go wrong: tiles of every shape, extents
+they do not divide, boxes of one chunk and of a padded last chunk, windows that
+span their axis (even ones too), each number of waves per tile, every head_dim.
+
+Tolerances: float32 data 1e-5; bf16 outputs one rounding of a float32 result, that is
+half a bf16 ulp of the exact value plus the same 1e-5; bf16 gradients the parity rule
+(their D comes from the forward's output as it is stored)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_31248_amd import binding as B
+from paper_2606_31248_amd import inputs as I
+from _util import F32_ABS, bf16_half_ulp, check_close, host_f64
+from test_gpu_parity import gpu_phases, oracle_coords, run_bwd, run_fwd
+
+pytestmark = pytest.mark.gpu
+
+
+def close(got, ref, dtype, what):
+    tol = F32_ABS + (bf16_half_ulp(ref) * (1 + 2.0 ** -8) if dtype == "bf16" else 0.0)
+    worst = float(np.max(np.abs(got - ref) - tol))
+    assert worst <= 0, f"{what}: {worst:.3e} beyond the tolerance"
+
+
+SHAPES = [
+    # (shape, window): 256 tiles or fewer take four waves per tile
+    ((1, 1, 1, 1, 1, 64), (1, 1, 1), "f32"),       # one token
+    ((1, 2, 2, 3, 5, 128), (1, 3, 5), "bf16"),     # box = window, one padded chunk
+    ((2, 1, 3, 6, 7, 128), (3, 3, 7), "f32"),
+    ((1, 3, 18, 2, 3, 64), (18, 1, 1), "f32"),     # columns, an even window that spans its axis
+    ((1, 1, 33, 3, 2, 32), (9, 1, 1), "bf16"),     # columns beyond 32 levels
+    ((1, 2, 4, 6, 8, 32), (4, 6, 8), "f32"),       # every token sees every token
+    ((2, 2, 5, 17, 9, 64), (3, 3, 3), "bf16"),
+    ((1, 40, 6, 17, 19, 64), (3, 5, 5), "bf16"),   # two waves per tile
+    ((4, 16, 8, 17, 16, 32), (3, 3, 3), "f32"),    # one wave per tile
+]
+
+
+@pytest.mark.parametrize("shape,window,dtype", SHAPES)
+def test_forward_and_backward(shape, window, dtype):
+    c32 = oracle_coords(I.random_placement(shape[0], shape[3], shape[4], 97), shape[3], shape[4])
+    (q, k, v), out, lse, scale = run_fwd(shape, window, dtype, 51, c32)
+    wide = [oracle.widen(a, dtype) for a in (q, k, v)]
+    ro, rl = oracle.na3d_fwd(*wide, window, scale, coords=c32)
+    close(host_f64(out), ro, dtype, "out")
+    assert np.max(np.abs(host_f64(lse) - rl)) <= 1e-5
+    (q, k, v, g), grads, scale = run_bwd(shape, window, dtype, 52, c32)
+    refs = oracle.na3d_bwd(*(oracle.widen(a, dtype) for a in (q, k, v, g)), window, scale, coords=c32)
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, refs):
+        check_close(host_f64(got), ref, dtype, name)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 32)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_values_that_are_not_finite_stay_in_their_windows(dtype, d, bad):
+    """One token of each of q, k, v, dO holds inf or NaN: the results that the oracle gives as finite (their
+    windows hold none of these) are the oracle's, the others are not finite."""
+    shape, window = (1, 1, 5, 16, 15, d), (3, 5, 5)
+    names = ("q", "k", "v", "g")
+    host = {n: oracle.widen(I.gaussian(shape, 61, s, dtype), dtype) for s, n in enumerate(names)}
+    at = {"q": (0, 2, 2), "k": (4, 15, 14), "v": (2, 0, 14), "g": (2, 12, 1)}
+    for n in names:
+        host[n][(0, 0) + at[n] + (7,)] = bad
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    qd, kd, vd, gd = (torch.from_numpy(host[n]).to(dt).cuda() for n in names)
+    scale = d ** -0.5
+    desc = B.desc_for(qd, window, scale)
+    out = torch.empty_like(qd)
+    lse = torch.empty(shape[:-1], dtype=torch.float32, device="cuda")
+    B.strata_na3d_fwd(desc, qd, kd, vd, None, out, lse)
+    grads = [torch.empty_like(qd) for _ in range(3)]
+    ws = torch.empty(B.strata_na3d_bwd_workspace_size(desc), dtype=torch.uint8, device="cuda")
+    B.strata_na3d_bwd(desc, qd, kd, vd, None, out, gd, lse, *grads, ws)
+    with np.errstate(all="ignore"):
+        ro, _ = oracle.na3d_fwd(*(host[n] for n in names[:3]), window, scale)
+        refs = oracle.na3d_bwd(*(host[n] for n in names), window, scale)
+    for name, got, ref in zip(("out", "dq", "dk", "dv"), [out] + grads, (ro,) + tuple(refs)):
+        got = host_f64(got)
+        fine = np.isfinite(ref)
+        assert 0 < np.count_nonzero(~fine) < ref.size // 2
+        assert np.array_equal(np.isfinite(got), fine), name
+        check_close(got[fine], ref[fine], dtype, name)
