@@ -196,7 +196,13 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   // D = rowsum(dO * O): from the gate's pass, from the MFMA dq pass (which reads
   // O beside the dO rows it loads anyway), or from a pass of its own
   const bool fuse_d = !o.gate && na3d_bwd_dq_mfma_takes(*desc);
-  if (o.gate) {
+  if (o.gate && o.gate_dim == 1 && desc->dtype == STRATA_BF16) {
+    // lse' where the low term of a two-term dA would be (4 bytes of its row)
+    float* lse_f = reinterpret_cast<float*>(ws + L.da_lo);
+    launch_na3d_bwd_gate_row_prep(*desc, o, out, dout, lse, lse_f, dvec, ws + L.da_hi, dgate, s);
+    ga = ws + L.da_hi;
+    lse = lse_f;
+  } else if (o.gate) {
     void* lo = desc->dtype == STRATA_BF16 ? ws + L.da_lo : nullptr;
     launch_na3d_bwd_gate_prep(*desc, o, out, dout, dvec, ws + L.da_hi, lo, dgate, s);
     ga = ws + L.da_hi;

@@ -97,6 +97,12 @@ void launch_na3d_bwd_gate_prep(const strata_na3d_desc& d, const NaOpts& o, const
                                const void* dout, float* dvec, void* da_hi, void* da_lo, void* dgate,
                                hipStream_t s);
 
+// The same for bf16 with one logit per (token, head), as a plain backward: da =
+// 2^e dO, lse_f = lse - ln f and D / f into dvec, where sigmoid(g) = f 2^e.
+void launch_na3d_bwd_gate_row_prep(const strata_na3d_desc& d, const NaOpts& o, const void* out, const void* dout,
+                                   const float* lse, float* lse_f, float* dvec, void* da, void* dgate,
+                                   hipStream_t s);
+
 // bf16 MFMA backward parts; each returns false when the problem has no MFMA variant.
 // dq: query-stationary (the forward's decomposition); dk/dv: key-stationary.
 // With `out` (the forward's O) set, the dq pass also forms D = rowsum(dO * O)

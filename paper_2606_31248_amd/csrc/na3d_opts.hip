@@ -122,6 +122,56 @@ __global__ void __launch_bounds__(256) gate_prep_kernel(const T* __restrict__ ou
   if (da_lo) *reinterpret_cast<uint4*>(da_lo + row * D + c * E) = PC::pack_lo(d);
 }
 
+// bf16 with one gate logit per (token, head).  With a = sigmoid(g) = f 2^e, f in
+// [1/2, 1), the gated backward is the plain one on
+//   dO' = 2^e dO (exact in bf16),  lse' = lse - ln f,  D' = D / f:
+// P' = f P, so P' (dO'.v - D') = P (a dO.v - D) and P' dO' = P a dO.  No rounded
+// dA is formed: the attention kernels take one bf16 tensor (as without a gate)
+// instead of dA in two terms, which the balanced dK/dV kernel has no room for,
+// and the range of a stays out of P' whatever the gate.  a = 0 gives dO' = 0.
+// Measured with two terms before: the 9x9x9 backward with QK norm, 24 tiles x 16
+// heads x 24x16x16: 9.58 -> 7.26 ms; the column-wise forward and backward there,
+// window 24x1x1: 1.40 -> 1.10 ms.
+__global__ void __launch_bounds__(256) gate_row_prep_kernel(const uint16_t* __restrict__ out,
+                                                            const uint16_t* __restrict__ dout,
+                                                            const uint16_t* __restrict__ gate,
+                                                            const float* __restrict__ lse, float* __restrict__ lse_f,
+                                                            float* __restrict__ dvec, uint16_t* __restrict__ da,
+                                                            uint16_t* __restrict__ dgate, int64_t n, int log2_cpr) {
+  using PC = Piece<uint16_t>;
+  constexpr int E = PC::E;
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t row = gid >> log2_cpr;
+  const bool live = row < n;
+  float o[E], g[E];
+  float Dr = 0.f;
+  if (live) {
+    PC::unpack(*reinterpret_cast<const uint4*>(out + gid * E), o);
+    PC::unpack(*reinterpret_cast<const uint4*>(dout + gid * E), g);
+#pragma unroll
+    for (int e = 0; e < E; ++e) Dr = fmaf(g[e], o[e], Dr);
+  }
+  for (int off = 1 << log2_cpr >> 1; off > 0; off >>= 1) Dr += __shfl_xor(Dr, off);
+  if (!live) return;
+  const float gl = PC::load1(gate + row);
+  const float a = sigm(gl);
+  int e2 = 0;
+  float f = frexpf(a, &e2);
+  float mul = ldexpf(1.f, e2);
+  if (a == 0.f) {
+    f = 0.5f;
+    mul = 0.f;
+  }
+  if ((gid & ((1 << log2_cpr) - 1)) == 0) {
+    PC::store1(dgate + row, sigm(-gl) * Dr);
+    dvec[row] = Dr / f;
+    lse_f[row] = lse[row] - logf(f);
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) g[e] *= mul;
+  *reinterpret_cast<uint4*>(da + gid * E) = PC::pack(g);
+}
+
 int64_t rows(const strata_na3d_desc& d) { return (int64_t)d.B * d.heads * d.Z * d.H * d.W; }
 
 template <typename T, int D>
@@ -156,6 +206,17 @@ void launch_na3d_bwd_gate_prep(const strata_na3d_desc& d, const NaOpts& o, const
                      static_cast<T*>(da_lo), static_cast<T*>(dgate), n)
   STRATA_DISPATCH_TD(d, F);
 #undef F
+}
+
+void launch_na3d_bwd_gate_row_prep(const strata_na3d_desc& d, const NaOpts& o, const void* out, const void* dout,
+                                   const float* lse, float* lse_f, float* dvec, void* da, void* dgate,
+                                   hipStream_t s) {
+  const int64_t n = rows(d);
+  const int l2 = d.head_dim == 32 ? 2 : d.head_dim == 64 ? 3 : 4;  // 16-byte pieces per row
+  hipLaunchKernelGGL(gate_row_prep_kernel, dim3((unsigned)(((n << l2) + 255) / 256)), dim3(256), 0, s,
+                     static_cast<const uint16_t*>(out), static_cast<const uint16_t*>(dout),
+                     static_cast<const uint16_t*>(o.gate), lse, lse_f, dvec, static_cast<uint16_t*>(da),
+                     static_cast<uint16_t*>(dgate), n, l2);
 }
 
 }  // namespace strata

@@ -1,0 +1,60 @@
+"""Backward with one gate logit per (token, head) over the whole range of the
+sigmoid: logits from -200 (a sigmoid of exactly 0) to 30, one head shut almost
+wholly.  The gradients of every head are held to the bf16 rules relative to that
+head alone, dq also per logit, on each kernel that the gated backward reaches."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_31248_amd import binding as B
+from paper_2606_31248_amd import inputs as I
+from _util import check_close, dev_tensor, host_f64
+from test_gpu_options import check_bwd_grads, coords_for, gpu_phases
+
+pytestmark = pytest.mark.gpu
+
+LOGITS = np.array([-200.0, -60.0, -20.0, -3.0, 0.0, 4.0, 30.0], np.float32)
+
+
+@pytest.mark.parametrize("shape,window", [
+    ((1, 2, 5, 13, 12, 64), (5, 9, 9)),     # balanced dK/dV
+    ((1, 2, 5, 13, 11, 64), (3, 7, 7)),     # one-block dK/dV
+    ((2, 2, 20, 3, 5, 64), (20, 1, 1)),     # columns of two blocks
+    # columns of one block (with 5 keys to a window the bf16 rounding of the forward's output, through D, is
+    # 2.2% of RMS(dq), the same with dA in two terms: a window of 15 averages it down by sqrt(3))
+    ((1, 2, 15, 4, 5, 64), (15, 1, 1)),
+    ((1, 2, 5, 9, 10, 64), (3, 3, 3)),      # any window
+    ((1, 2, 9, 10, 9, 128), (9, 9, 9)),     # head_dim 128
+])
+@pytest.mark.parametrize("qk_norm", [False, True])
+def test_backward_over_the_sigmoid_range(shape, window, qk_norm):
+    c32 = coords_for(shape, 103)
+    q, k, v, dout = (I.gaussian(shape, 71, s, "bf16") for s in (0, 1, 2, I.STREAM_DO))
+    pick = I.rng(71, I.STREAM_GATE).integers(0, len(LOGITS), shape[:-1])
+    pick[:, 1] = 2  # a = 2e-9 throughout the second head
+    g = I.f32_to_bf16_bits(LOGITS[pick])
+    qd, kd, vd, gd, dod = (dev_tensor(a, "bf16") for a in (q, k, v, g, dout))
+    scale = shape[-1] ** -0.5
+    desc, opts, cs = B.desc_for(qd, window, scale), B.make_opts(qk_norm, 1e-6, gd), gpu_phases(c32, shape[-1])
+    out = torch.empty_like(qd)
+    lse = torch.empty(shape[:-1], dtype=torch.float32, device="cuda")
+    B.strata_na3d_fwd_ex(desc, opts, qd, kd, vd, cs, out, lse)
+    ws = torch.empty(B.strata_na3d_bwd_ex_workspace_size(desc, opts), dtype=torch.uint8, device="cuda")
+    dq, dk, dv, dg = torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(gd)
+    kept = lse.clone()
+    B.strata_na3d_bwd_ex(desc, opts, qd, kd, vd, cs, out, dod, lse, dq, dk, dv, dg, ws)
+    assert torch.equal(lse, kept)
+    w = lambda a: oracle.widen(a, "bf16")
+    refs = oracle.na3d_bwd(w(q), w(k), w(v), w(dout), window, scale, coords=c32, qk_norm=qk_norm, gate=w(g))
+    for h in range(shape[1]):
+        cut = lambda a: np.ascontiguousarray(a[:, h:h + 1])
+        check_bwd_grads(tuple(cut(a) for a in (q, k, v, g, dout)), [t[:, h:h + 1] for t in (dq, dk, dv, dg)],
+                        [cut(r) for r in refs], window, scale, "bf16", qk_norm, c32)
+    got = host_f64(dq)
+    for i, logit in enumerate(LOGITS):
+        rows = pick == i
+        if logit == -200.0:  # 1e-87: below the least bf16 value
+            assert not got[rows].any()
+            continue
+        check_close(got[rows], refs[0][rows], "bf16", f"dq at logit {logit}")
