@@ -21,9 +21,7 @@ LOGITS = np.array([-200.0, -60.0, -20.0, -3.0, 0.0, 4.0, 30.0], np.float32)
     ((1, 2, 5, 13, 12, 64), (5, 9, 9)),     # balanced dK/dV
     ((1, 2, 5, 13, 11, 64), (3, 7, 7)),     # one-block dK/dV
     ((2, 2, 20, 3, 5, 64), (20, 1, 1)),     # columns of two blocks
-    # columns of one block (with 5 keys to a window the bf16 rounding of the forward's output, through D, is
-    # 2.2% of RMS(dq), the same with dA in two terms: a window of 15 averages it down by sqrt(3))
-    ((1, 2, 15, 4, 5, 64), (15, 1, 1)),
+    ((1, 2, 9, 4, 5, 64), (5, 1, 1)),       # columns of one block
     ((1, 2, 5, 9, 10, 64), (3, 3, 3)),      # any window
     ((1, 2, 9, 10, 9, 128), (9, 9, 9)),     # head_dim 128
 ])
@@ -47,6 +45,16 @@ def test_backward_over_the_sigmoid_range(shape, window, qk_norm):
     assert torch.equal(lse, kept)
     w = lambda a: oracle.widen(a, "bf16")
     refs = oracle.na3d_bwd(w(q), w(k), w(v), w(dout), window, scale, coords=c32, qk_norm=qk_norm, gate=w(g))
+    if window[1] == 1 and not qk_norm:
+        # D_i = <dO_i, out_i> is that of the output as it is stored in bf16; with few keys to a window its rounding
+        # shows in dq and dk (2.2% and 2.7% of their RMS).  The exact results for that output differ by
+        # scale d_i sum_j P_ij k_j (the forward on v = k) and scale sum_i P_ij d_i q_i (dv for dO = d q), d = D - D_stored
+        # (the rotation cancels inside a column)
+        ro, _ = oracle.na3d_fwd(w(q), w(k), w(v), window, scale, gate=w(g))
+        d = ((ro - host_f64(out)) * w(dout)).sum(-1, keepdims=True)
+        pk, _ = oracle.na3d_fwd(w(q), w(k), w(k), window, scale)
+        pq = oracle.na3d_bwd(w(q), w(k), w(v), d * w(q), window, scale)[2]
+        refs = (refs[0] + scale * d * pk, refs[1] + scale * pq) + tuple(refs[2:])
     for h in range(shape[1]):
         cut = lambda a: np.ascontiguousarray(a[:, h:h + 1])
         check_bwd_grads(tuple(cut(a) for a in (q, k, v, g, dout)), [t[:, h:h + 1] for t in (dq, dk, dv, dg)],
