@@ -34,7 +34,7 @@ FLAGS = [
 
 # Per-file extra flags.  The attention kernel never sees NaN inputs by contract
 # (masked logits are -inf, not NaN), so max() needs no NaN canonicalisation.
-EXTRA = {"na3d_mfma_q.hip": ["-fno-honor-nans"], "na3d_mfma_d128.hip": ["-fno-honor-nans"], "na3d_bwd_d128.hip": ["-fno-honor-nans"], "na3d_col.hip": ["-fno-honor-nans"], "na3d_mfma_kv.hip": ["-fno-honor-nans"], "na3d_mfma_kvp.hip": ["-fno-honor-nans"],
+EXTRA = {"na3d_mfma_q.hip": ["-fno-honor-nans"], "na3d_mfma_d128.hip": ["-fno-honor-nans"], "na3d_bwd_d128.hip": ["-fno-honor-nans"], "na3d_col.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"], "na3d_mfma_kv.hip": ["-fno-honor-nans"], "na3d_mfma_kvp.hip": ["-fno-honor-nans"],
          # MFMA accumulators in VGPRs (the any-window kernels keep NaN semantics)
          "na3d_any.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          # the level-sweep forward: MFMA accumulators in VGPRs, so that the logits the

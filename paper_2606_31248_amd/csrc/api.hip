@@ -185,6 +185,8 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
                                      const void* q, const void* k, const void* v, const float* cs, const void* out,
                                      const void* dout, const float* lse, void* dq, void* dk, void* dv, void* dgate,
                                      char* ws, hipStream_t s) {
+  if (launch_na3d_bwd_col(*desc, o, q, k, v, out, dout, lse, dq, dk, dv, dgate, s))
+    return check_launch(opts ? "strata_na3d_bwd_ex" : "strata_na3d_bwd");
   const BwdLayout L = bwd_layout(*desc, o);
   float* dvec = reinterpret_cast<float*>(ws + L.dvec);
   // the attention backward runs with upstream gradient dA (dO without a gate);
@@ -210,8 +212,6 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   } else if (!fuse_d) {
     launch_na3d_bwd_any(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);
   }
-  if (launch_na3d_bwd_col(*desc, bo, q, k, v, ga, lse, dvec, dq, dk, dv, s))
-    return check_launch(opts ? "strata_na3d_bwd_ex" : "strata_na3d_bwd");
   // the MFMA dq pass also records the largest |dO| exponent per (batch, head)
   // when the balanced dk/dv pass, which scales its float16 copy of dO by it,
   // takes the problem

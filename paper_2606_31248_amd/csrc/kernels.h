@@ -117,11 +117,12 @@ bool launch_na3d_bwd_dq_mfma(const strata_na3d_desc& d, const BwdOpts& o, const 
                              const void* k, const void* v, const float* cs, const void* dout,
                              const float* lse, float* dvec, const void* out, int* emax, void* dq,
                              hipStream_t s);
-// bf16 column-wise backward (dq, dk, dv together), windows (kz, 1, 1) with Z <= 32,
-// head_dim 64; false for any other problem.
-bool launch_na3d_bwd_col(const strata_na3d_desc& d, const BwdOpts& o, const void* q, const void* k,
-                         const void* v, const void* dout, const float* lse, const float* dvec, void* dq,
-                         void* dk, void* dv, hipStream_t s);
+// bf16 column-wise backward (dq, dk, dv, dgate together, D and the gate's part
+// formed inside), windows (kz, 1, 1) with Z <= 32, head_dim 64; false for any
+// other problem.
+bool launch_na3d_bwd_col(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k, const void* v,
+                         const void* out, const void* dout, const float* lse, void* dq, void* dk, void* dv,
+                         void* dgate, hipStream_t s);
 // dK/dV with two key levels x four 4x4 blocks per workgroup (bf16, head_dim 64,
 // windows 5x9x9 and 9x9x9, no two-term dO); false if not applicable
 // (emax: the dO exponents the MFMA dq pass recorded; na3d_bwd_dkdv_kvp_takes

@@ -130,8 +130,7 @@ __global__ void __launch_bounds__(256) gate_prep_kernel(const T* __restrict__ ou
 // instead of dA in two terms, which the balanced dK/dV kernel has no room for,
 // and the range of a stays out of P' whatever the gate.  a = 0 gives dO' = 0.
 // Measured with two terms before: the 9x9x9 backward with QK norm, 24 tiles x 16
-// heads x 24x16x16: 9.58 -> 7.26 ms; the column-wise forward and backward there,
-// window 24x1x1: 1.40 -> 1.10 ms.
+// heads x 24x16x16: 9.58 -> 7.26 ms.
 __global__ void __launch_bounds__(256) gate_row_prep_kernel(const uint16_t* __restrict__ out,
                                                             const uint16_t* __restrict__ dout,
                                                             const uint16_t* __restrict__ gate,
