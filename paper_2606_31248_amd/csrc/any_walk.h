@@ -27,9 +27,11 @@ struct FastDiv {
 struct AnyDims {
   int heads, Z, H, W, kz, ky, kx;
   int lz, ly, lx;         // log2 extents of the 16-token tile
-  FastDiv tz, ty, tx;     // tiles per axis
-  int64_t tiles;          // of the whole problem
-  int split;              // waves that share a tile's chunks (1, 2 or 4)
+  FastDiv ty, tx;         // tiles along y and x
+  FastDiv places;         // tiles of one grid
+  uint32_t nbh;           // grids: batch * heads
+  int split;              // waves of a workgroup that share a tile's chunks (1, 2 or 4); the others take the
+                          // same tile of the next 4 / split grids
   float scale;
   int norm;
   float eps;
@@ -41,10 +43,8 @@ __host__ __device__ __forceinline__ int start(int i, int L, int k) {
   return s < 0 ? 0 : s > L - k ? L - k : s;
 }
 
-// The wave's tile and the box it walks.
+// A tile and the box it walks (the same in every batch and head).
 struct Walk {
-  int64_t bh;       // batch * heads + head
-  int b;
   int z, y, x;      // the lane's token of the tile (column m), clamped into the grid
   bool live;        // that token lies inside the grid
   int oz, oy, ox;   // origin of the box
@@ -84,16 +84,14 @@ struct Walk {
   }
   template <bool INV>
   static __host__ __device__ __forceinline__ Walk make(const AnyDims& d, uint32_t tile, int m) {
-    uint32_t t = tile;
-    const uint32_t q0 = d.tx.div(t), ix = t - q0 * d.tx.n;
-    const uint32_t q1 = d.ty.div(q0), iy = q0 - q1 * d.ty.n;
-    const uint32_t q2 = d.tz.div(q1), iz = q1 - q2 * d.tz.n;
+    const uint32_t q0 = d.tx.div(tile), ix = tile - q0 * d.tx.n;
+    const uint32_t iz = d.ty.div(q0), iy = q0 - iz * d.ty.n;
     int z, y, x, oz, oy, ox, lz, ly, lx, cz, cy, cx;
     bool live = true;
     const int nz = axis<INV>((int)iz, d.lz, d.Z, d.kz, m >> (d.lx + d.ly), z, live, oz, lz, cz);
     const int ny = axis<INV>((int)iy, d.ly, d.H, d.ky, (m >> d.lx) & ((1 << d.ly) - 1), y, live, oy, ly, cy);
     const int nx = axis<INV>((int)ix, d.lx, d.W, d.kx, m & ((1 << d.lx) - 1), x, live, ox, lx, cx);
-    return Walk{(int64_t)q2, (int)(q2 / (uint32_t)d.heads), z, y, x, live, oz, oy, ox, ny, nx,
+    return Walk{z, y, x, live, oz, oy, ox, ny, nx,
                 FastDiv((uint32_t)(ny * nx)), FastDiv((uint32_t)nx), (uint32_t)(nz * ny * nx),
                 lz, ly, lx, cz, cy, cx, d.H, d.W};
   }
@@ -113,28 +111,50 @@ struct Walk {
   __host__ __device__ __forceinline__ uint32_t mine_in_plane() const { return (uint32_t)y * (uint32_t)W + (uint32_t)x; }
   __host__ __device__ __forceinline__ uint32_t mine() const { return (uint32_t)z * ((uint32_t)H * (uint32_t)W) + mine_in_plane(); }
   __host__ __device__ __forceinline__ bool sees(int bz, int by, int bx) const {
-    return (uint32_t)(bz - lz) < (uint32_t)cz && (uint32_t)(by - ly) < (uint32_t)cy && (uint32_t)(bx - lx) < (uint32_t)cx;
+    return ((uint32_t)(bz - lz) < (uint32_t)cz) & ((uint32_t)(by - ly) < (uint32_t)cy) & ((uint32_t)(bx - lx) < (uint32_t)cx);
   }
-  // the chunk's tokens 4g + r: grid position (clamped into the box) and whether the lane's token sees it
-  __host__ __device__ __forceinline__ void four(uint32_t i, uint32_t* tk, bool* in) const {
+  // bit r: token i + r of the box exists and the lane's token sees it
+  __host__ __device__ __forceinline__ uint32_t four(uint32_t i) const {
     int bz, by, bx;
     at(min(i, n - 1), bz, by, bx);
+    uint32_t bits = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      tk[r] = tok(bz, plane(by, bx));
-      in[r] = i + r < n && sees(bz, by, bx);
-      if (i + r + 1 < n) {
-        if (++bx == nx) {
-          bx = 0;
-          if (++by == ny) {
-            by = 0;
-            ++bz;
-          }
-        }
-      }
+      bits |= (uint32_t)((i + r < n) & sees(bz, by, bx)) << r;
+      const bool ex = ++bx == nx;
+      by += ex;
+      bx = ex ? 0 : bx;
+      const bool ey = by == ny;
+      bz += ey;
+      by = ey ? 0 : by;
     }
+    return bits;
   }
 };
+
+// A run of chunks of the box, kept in LDS by the waves of a workgroup (they walk
+// the same tile): grid position and plane position of every token (clamped into
+// the box), and per chunk and lane (m, g) which of the chunk's tokens 4g + r the
+// tile's token m sees.
+constexpr int kRun = 32;
+struct Run {
+  uint32_t tok[16 * kRun], pl[16 * kRun];
+  uint8_t see[64 * kRun];
+};
+
+// the part of thread tid of 256 (its lane is the walk's) in filling a run from token i0 of the box on
+__host__ __device__ __forceinline__ void fill_run(const Walk& w, Run& t, uint32_t i0, int tid) {
+  const uint32_t left = w.n - i0;
+  for (uint32_t j = tid; j < 16 * kRun && j < ((left + 15) & ~15u); j += 256) {
+    int bz, by, bx;
+    w.at(min(i0 + j, w.n - 1), bz, by, bx);
+    const uint32_t p = w.plane(by, bx);
+    t.pl[j] = p;
+    t.tok[j] = w.tok(bz, p);
+  }
+  for (uint32_t c = tid >> 6; c < kRun && 16 * c < left; c += 4)
+    t.see[64 * c + (tid & 63)] = (uint8_t)w.four(i0 + 16 * c + 4 * ((tid & 63) >> 4));
+}
 
 // Tokens that a block of b positions of an axis reaches, at most
 inline int box_extent(int b, int L, int k) { return L < b + k - 1 ? L : b + k - 1; }
@@ -160,20 +180,30 @@ inline AnyDims any_dims(int B, int heads, int Z, int H, int W, int kz, int ky, i
       }
     }
   auto count = [](int L, int l) { return FastDiv((uint32_t)(((int64_t)L + (1 << l) - 1) >> l)); };
-  tiles *= (int64_t)B * heads;
-  // Fewer tiles than 4 waves per SIMD of the 256 CUs: 2 or 4 waves share a tile's chunks
-  const int split = tiles >= 4096 ? 1 : tiles >= 2048 ? 2 : 4;
-  return AnyDims{heads, Z, H, W, kz, ky, kx, best[0], best[1], best[2], count(Z, best[0]),
-                 count(H, best[1]), count(W, best[2]), tiles, split, scale, norm, eps};
+  const int64_t nbh = (int64_t)B * heads;
+  // Fewer tiles than 4 waves per SIMD of the 256 CUs, or grids that do not fill
+  // the workgroups' other waves (more than 15% of them idle): 2 or 4 waves share
+  // a tile's chunks
+  int split = tiles * nbh >= 4096 ? 1 : tiles * nbh >= 2048 ? 2 : 4;
+  auto idle = [nbh](int per) { return (nbh + per - 1) / per * per * 20 > nbh * 23; };
+  while (split < 4 && idle(4 / split)) split *= 2;
+  return AnyDims{heads, Z, H, W, kz, ky, kx, best[0], best[1], best[2], count(H, best[1]), count(W, best[2]),
+                 FastDiv((uint32_t)tiles), (uint32_t)nbh, split, scale, norm, eps};
 }
 
-// Whether the 32-bit token indices and chunk counts above hold: every grid that a
-// device can hold (a 2^32-token tensor of the narrowest rows is 256 GiB).
+// workgroups of a problem: every tile of a grid for one group of grids, then the next group
+inline int64_t any_blocks(const AnyDims& d) {
+  const int64_t per = 4 / d.split;
+  return ((int64_t)d.nbh + per - 1) / per * d.places.n;
+}
+
+// Whether the 32-bit token and block indices above hold: every problem that a
+// device can hold (2^32 tokens of the narrowest rows are 256 GiB a tensor).
 inline bool any_fits(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
   // a box spans at most 16 + 1.5 k positions of an axis (the queries that see keys near a border)
   auto most = [](int L, int k) { return (double)(L < 16 + k + k / 2 ? L : 16 + k + k / 2); };
-  return (double)Z * H * W < 4294967296.0 && most(Z, kz) * most(H, ky) * most(W, kx) < 1073741824.0 &&
-         any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f).tiles < ((int64_t)1 << 30);
+  return (double)B * heads * Z * H * W < 4294967296.0 && most(Z, kz) * most(H, ky) * most(W, kx) < 1073741824.0 &&
+         any_blocks(any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f)) < ((int64_t)1 << 30);
 }
 
 }  // namespace any

@@ -64,8 +64,6 @@ static strata_status check_desc(const strata_na3d_desc* d) {
   REQUIRE(n * d->head_dim < kMaxElems, "desc: tensor too large");
   if (d->head_dim != 32 && d->head_dim != 64 && d->head_dim != 128)
     return set_error(STRATA_ERR_UNSUPPORTED, "head_dim %d not supported (32, 64 or 128)", d->head_dim);
-  // grids that no device holds: the kernels index a tile's tokens with 32 bits
-  if (!na3d_any_takes(*d)) return set_error(STRATA_ERR_UNSUPPORTED, "desc: grid too large for 32-bit token indices");
   return STRATA_OK;
 }
 
@@ -111,6 +109,12 @@ static BwdLayout bwd_layout(const strata_na3d_desc& d, const NaOpts& o) {
   return L;
 }
 
+// problems that no device holds: the any-window kernels index tokens with 32 bits
+#define REQUIRE_FITS(d)                                                                                     \
+  do {                                                                                                      \
+    if (!na3d_any_takes(d)) return set_error(STRATA_ERR_UNSUPPORTED, "desc: more tokens than 32 bits index"); \
+  } while (0)
+
 // the forward kernel for the problem's shape
 static void launch_fwd(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k, const void* v,
                        const float* cs, void* out, float* lse, hipStream_t s) {
@@ -134,6 +138,7 @@ static strata_status na3d_fwd_impl(const strata_na3d_desc* desc, const strata_na
   REQUIRE_PTR(out);
   if (cs) REQUIRE(aligned16(cs), "cs: not 16-byte aligned");
   if (lse) REQUIRE(aligned16(lse), "lse: not 16-byte aligned");
+  REQUIRE_FITS(*desc);
   launch_fwd(*desc, o, q, k, v, cs, out, lse, (hipStream_t)stream);
   return check_launch(opts ? "strata_na3d_fwd_ex" : "strata_na3d_fwd");
 }
@@ -177,6 +182,7 @@ static strata_status na3d_bwd_impl(const strata_na3d_desc* desc, const strata_na
     return set_error(STRATA_ERR_WORKSPACE, "workspace: need %zu bytes, got %zu", L.total,
                      workspace ? workspace_bytes : (size_t)0);
   REQUIRE(aligned16(workspace), "workspace: not 16-byte aligned");
+  REQUIRE_FITS(*desc);
   return na3d_bwd_launch(desc, opts, o, q, k, v, cs, out, dout, lse, dq, dk, dv, dgate, static_cast<char*>(workspace),
                          (hipStream_t)stream);
 }
@@ -276,6 +282,7 @@ static strata_status na3d_bwd_noalloc_impl(const strata_na3d_desc* desc, const v
           "bwd_noalloc: %lld token-heads (%lld batch-heads) exceed the static scratch of %lld (%lld) (use "
           "strata_na3d_bwd with a workspace)",
           (long long)n, (long long)bh, (long long)kMaxTokenHeads, (long long)kMaxBatchHeads);
+  REQUIRE_FITS(*desc);
   const NaOpts o;
   REQUIRE(bwd_layout(*desc, o).total <= (size_t)kScratchFloats * sizeof(float), "bwd_noalloc: static scratch layout");
   int dev = 0;
@@ -522,6 +529,7 @@ strata_status strata_na3d_fwd_stitch(const strata_na3d_desc* desc, const strata_
   REQUIRE((int64_t)Wf * C < ((int64_t)1 << 31) &&
               (int64_t)P * Hf * (((int64_t)Wf * C + 255) / 256) < ((int64_t)1 << 31),
           "fwd_stitch: face too large for one launch");
+  REQUIRE_FITS(*desc);
   hipStream_t s = (hipStream_t)stream;
   const StitchArgs sa = {face, window, nty, ntx, stride_y, stride_x, Hf, Wf};
   const bool fused = overlap_form(nty, ntx, Ht, Wt, C, stride_y, stride_x, Hf, Wf, desc->dtype) &&

@@ -5,12 +5,15 @@
 // a large matrix product), so nothing is rounded to 16 bits between the inputs
 // and the results.
 //
-// A wave owns a tile of 16 tokens (queries in the forward and dq, keys in dk/dv)
-// in a block of (z, y, x) extents whose product is 16, and walks the box of
-// tokens on the other side that any of them sees, 16 at a time (a chunk), in
-// linear order over the whole three-dimensional box, so that at most one chunk
-// is padded.  What bounds it: the matrix instructions, 2 head_dim / 4 per chunk
-// forward, 3 in dq, 4 in dk/dv, times the share of the box outside the windows.
+// A workgroup owns a tile of 16 tokens (queries in the forward and dq, keys in
+// dk/dv), a block of (z, y, x) extents whose product is 16; its four waves take
+// the tile in four (batch, head) grids, or share its work in two or one.  A wave
+// walks the box of tokens on the other side that any of the 16 sees, 16 at a time
+// (a chunk), in linear order over the whole three-dimensional box, so that at most
+// one chunk is padded; positions and window masks, the same in every grid, are
+// formed once by the four waves in LDS.  What bounds it: matrix and vector
+// instructions add up (a float32 matrix instruction takes 32 cycles, head_dim / 4
+// of them per chunk and product), times the share of the box outside the windows.
 //
 // Layouts (lane l, m = l % 16, g = l / 16).  A 16 x 4 operand gives lane l row m,
 // column g.  The sum over head_dim may take the channels in any order, so lane l
@@ -25,9 +28,10 @@
 //
 // Measured against one thread per query (or one wave per query below 2^18) with
 // float32 vector arithmetic: float32 forward and backward, 4 heads x 7x21x27,
-// d 64, 5x9x9: 14733 -> 243 us; bf16 3x3x3 forward and backward, 6 tiles x 16
-// heads x 24x16x16: 20589 -> 1180 us; float32 forward, 4 heads x 4x16x16, d 32,
-// 3x7x7: 56.8 -> 13.6 us.
+// d 64, 5x9x9: 14733 -> 250 us; bf16 3x3x3 forward and backward, 6 tiles x 16
+// heads x 24x16x16: 20589 -> 868 us (1104 us with each wave forming its own
+// positions and masks, 1015 us with every product in float32); float32 forward,
+// 4 heads x 4x16x16, d 32, 3x7x7: 56.8 -> 13.8 us.
 //
 // Values outside a query's window never reach its results, infinities and NaN
 // included: scores and weights are selected, and a chunk that holds a value that
@@ -56,6 +60,21 @@ __device__ __forceinline__ float ldf<float>(const float* p) { return *p; }
 template <>
 __device__ __forceinline__ float ldf<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 
+// N values from their storage words
+template <typename T, int N>
+__device__ __forceinline__ void widen_n(const uint32_t* u, float* f) {
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = __uint_as_float(u[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; i += 2) {
+      f[i] = __uint_as_float(u[i / 2] << 16);
+      f[i + 1] = __uint_as_float(u[i / 2] & 0xFFFF0000u);
+    }
+  }
+}
+
 // N consecutive values, N sizeof(T) a multiple of 4 and the address aligned to it (at most 16)
 template <typename T, int N>
 __device__ __forceinline__ void load_n(const T* p, float* f) {
@@ -74,16 +93,7 @@ __device__ __forceinline__ void load_n(const T* p, float* f) {
     static_assert(W == 1, "");
     u[0] = *reinterpret_cast<const uint32_t*>(p);
   }
-  if constexpr (sizeof(T) == 4) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) f[i] = __uint_as_float(u[i]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; i += 2) {
-      f[i] = __uint_as_float(u[i / 2] << 16);
-      f[i + 1] = __uint_as_float(u[i / 2] & 0xFFFF0000u);
-    }
-  }
+  widen_n<T, N>(u, f);
 }
 
 template <typename T, int N>
@@ -105,16 +115,46 @@ struct Frag {
   static constexpr int E = 16 / (int)sizeof(T);  // elements of a piece
   static constexpr int NP = D / (4 * E);         // pieces per lane
   static constexpr int N = D / 4;                // elements per lane
-  static __device__ __forceinline__ void load(const T* row, int g, float* f) {
+  struct Raw {
+    uint4 v[NP];
+  };
+  struct Phases {
+    float4 v[N / 4];
+  };
+  static __device__ __forceinline__ void load(const T* row, int g, Raw& r) {
 #pragma unroll
-    for (int j = 0; j < NP; ++j) load_n<T, E>(row + (4 * j + g) * E, f + j * E);
+    for (int j = 0; j < NP; ++j) r.v[j] = *reinterpret_cast<const uint4*>(row + (4 * j + g) * E);
+  }
+  static __device__ __forceinline__ void widen(const Raw& r, float* f) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const uint32_t u[4] = {r.v[j].x, r.v[j].y, r.v[j].z, r.v[j].w};
+      widen_n<T, E>(u, f + j * E);
+    }
+  }
+  static __device__ __forceinline__ void load(const T* row, int g, float* f) {
+    Raw r;
+    load(row, g, r);
+    widen(r, f);
+  }
+  static __device__ __forceinline__ void load_phases(const float2* ph, int g, Phases& p) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j)
+#pragma unroll
+      for (int e = 0; e < E; e += 4)
+        p.v[(j * E + e) / 4] = *reinterpret_cast<const float4*>(ph + ((4 * j + g) * E + e) / 2);
   }
   static __device__ __forceinline__ void rotate(const float2* ph, int g, float* f) {
+    Phases p;
+    load_phases(ph, g, p);
+    rotate(p, f);
+  }
+  static __device__ __forceinline__ void rotate(const Phases& ph, float* f) {
 #pragma unroll
     for (int j = 0; j < NP; ++j)
 #pragma unroll
       for (int e = 0; e < E; e += 4) {
-        const float4 p = *reinterpret_cast<const float4*>(ph + ((4 * j + g) * E + e) / 2);
+        const float4 p = ph.v[(j * E + e) / 4];
         float* x = f + j * E + e;
         const float a = x[0], b = x[1], c = x[2], d = x[3];
         x[0] = fmaf(a, p.x, -b * p.y);
@@ -150,21 +190,78 @@ __device__ __forceinline__ float not_finite(const float* f, float t) {
   return t;
 }
 
+// Channel of element i of a lane's output tile c: the lane holds the 4 CPL
+// channels from 4 CPL g on, tile by tile with products of bf16 rows (X), element
+// by element with float32 ones.
+template <int CPL, bool X>
+__device__ __forceinline__ constexpr int channel(int g, int c, int i) {
+  return 4 * CPL * g + (X ? 4 * c + i : CPL * i + c);
+}
+
+// ---- products with rows that are bf16 as they come ----------------------------
+// A product of two bf16 values is exact in float32, so V . dO^T takes the raw
+// rows on the bf16 instruction (16 times the float32 rate), and P . V, dO^T . P
+// take the float32 weights as three bf16 terms that add up to them (8 bits each,
+// 2^-25 left) against the raw rows: sums of exact products in float32, as before.
+template <int NP>
+__device__ __forceinline__ f32x4 contract16(const uint4 (&a)[NP], const uint4 (&b)[NP]) {
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < NP; ++j)
+    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mfma::bf16x8, a[j]),
+                                                __builtin_bit_cast(mfma::bf16x8, b[j]), s, 0, 0, 0);
+  return s;
+}
+
+// bytes of a staged bf16 row
+constexpr int row16(int D) { return 2 * D + 16; }
+
+// the lane's pieces of row m of a chunk, to its wave's tile of bf16 rows
+template <int NP>
+__device__ __forceinline__ void to_lds16(char* tile, int m, int g, const uint4 (&r)[NP]) {
+#pragma unroll
+  for (int j = 0; j < NP; ++j) mfma::st16(tile + m * row16(32 * NP) + 16 * (4 * j + g), r[j]);
+}
+
+// acc += rows^T w, rows: the wave's tile of bf16 rows, read transposed (tile c,
+// row m: channel 4 CPL (m / 4) + 4 c + m % 4)
+template <int CPL>
+__device__ __forceinline__ void add_product16(f32x4 (&acc)[CPL], const char* tile, int m, int g, const float* w) {
+  mfma::i16x4 t[3];
+  float x[4] = {w[0], w[1], w[2], w[3]};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t a = mfma::pack2(x[0], x[1]), b = mfma::pack2(x[2], x[3]);
+    t[k] = __builtin_bit_cast(mfma::i16x4, make_uint2(a, b));
+    x[0] -= mfma::lo_bf16(a);
+    x[1] -= mfma::hi_bf16(a);
+    x[2] -= mfma::lo_bf16(b);
+    x[3] -= mfma::hi_bf16(b);
+  }
+  const char* p = tile + (4 * g + (m >> 2)) * row16(16 * CPL) + 8 * CPL * (m & 3);
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    const mfma::i16x4 r = mfma::tr_read(p + 8 * c);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(r, t[k], acc[c], 0, 0, 0);
+  }
+}
+
 // acc += rows^T w over the chunk's 16 tokens, only those in the window: the path
 // of a chunk with a value that is not finite.  row(j, r, e): channel e of token
 // 4j + r of the chunk.
-template <int CPL, typename F>
-__device__ __forceinline__ void add_in_window(f32x4 (&acc)[CPL], const float* w, const bool* in, int m, int g, F row) {
+template <int CPL, bool X, typename F>
+__device__ __forceinline__ void add_in_window(f32x4 (&acc)[CPL], const float* w, uint32_t see, int m, int g, F row) {
 #pragma unroll 1
   for (int j = 0; j < 4; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float wj = __shfl(w[r], 16 * j + m);
-      const bool use = __shfl(in[r] ? 1 : 0, 16 * j + m) != 0;
+      const bool use = (__shfl((int)see, 16 * j + m) >> r) & 1;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c][i] = use ? fmaf(wj, row(j, r, CPL * (4 * g + i) + c), acc[c][i]) : acc[c][i];
+        for (int c = 0; c < CPL; ++c) acc[c][i] = use ? fmaf(wj, row(j, r, channel<CPL, X>(g, c, i)), acc[c][i]) : acc[c][i];
     }
 }
 
@@ -196,13 +293,41 @@ __device__ __forceinline__ uint32_t xcd_block() {
   return x * q + min(x, r) + blockIdx.x / 8;
 }
 
-// The wave's tile; waves past the last tile repeat it and store nothing.
-__device__ __forceinline__ uint32_t wave_tile(const AnyDims& d, int wave, int& part, bool& store) {
-  const int per = 4 / d.split;
-  const uint32_t t = xcd_block() * per + wave / d.split, n = (uint32_t)d.tiles;
-  part = wave % d.split;
-  store = t < n && part == 0;
-  return min(t, n - 1);
+// The workgroup's tile (a place in the grid), and the wave's grid (batch * heads +
+// head) and part of the chunks; waves past the last grid repeat it and store nothing.
+struct Place {
+  uint32_t tile;
+  int64_t bh;
+  int b, part;
+  bool store;
+};
+__device__ __forceinline__ Place wave_place(const AnyDims& d, int wave) {
+  const uint32_t blk = xcd_block(), grp = d.places.div(blk), bh = grp * (4 / d.split) + wave / d.split;
+  const uint32_t in = min(bh, d.nbh - 1);
+  const int part = wave % d.split;
+  return Place{blk - grp * d.places.n, (int64_t)in, (int)(in / (uint32_t)d.heads), part, bh < d.nbh && part == 0};
+}
+
+// body(c, see): every chunk of the wave's part of the box, in runs that the
+// workgroup's waves fill together; c: the chunk's place in the run, see: the
+// lane's four bits.  Every wave of the workgroup passes every barrier.
+template <typename F>
+__device__ __forceinline__ void walk_box(const Walk& w, Run& run, const AnyDims& d, int part, int lane, F body) {
+#pragma unroll 1
+  for (uint32_t i0 = 0; i0 < w.n; i0 += 16 * kRun) {
+    if (i0) __syncthreads();
+    fill_run(w, run, i0, threadIdx.x);
+    __syncthreads();
+    const uint32_t end = min((uint32_t)kRun, (w.n - i0 + 15) / 16);
+#pragma unroll 1
+    for (uint32_t c = part; c < end; c += d.split) body(c, run.see[64 * c + lane]);
+  }
+}
+
+// x where bit r is set, else `other`
+__device__ __forceinline__ float pick(uint32_t see, int r, float x, float other) {
+  const uint32_t sel = (uint32_t)__builtin_amdgcn_sbfe((int)see, r, 1);
+  return __uint_as_float((sel & __float_as_uint(x)) | (~sel & __float_as_uint(other)));
 }
 
 // ---- forward ---------------------------------------------------------------
@@ -212,16 +337,18 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
                                                            T* __restrict__ out, float* __restrict__ lse, AnyDims d,
                                                            const T* __restrict__ gate, int gate_dim) {
   using Fr = Frag<T, D>;
+  constexpr bool X = sizeof(T) == 2;
   constexpr int CPL = D / 16, NS = 4 * CPL + 2;
   __shared__ float merge[3 * 64 * NS];
+  __shared__ __attribute__((aligned(16))) char tv[4][X ? 16 * row16(D) : 16];
+  __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  int part;
-  bool store;
-  const uint32_t tile = wave_tile(d, wave, part, store);
-  const Walk w = Walk::make<false>(d, tile, m);
-  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = w.bh * n_tok;
+  const Place at = wave_place(d, wave);
+  const int part = at.part;
+  const Walk w = Walk::make<false>(d, at.tile, m);
+  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
   const uint32_t mine = w.mine();
-  const float2* ph = cs ? cs + (int64_t)w.b * d.H * d.W * (D / 2) : nullptr;
+  const float2* ph = cs ? cs + (int64_t)at.b * d.H * d.W * (D / 2) : nullptr;
   const T *kb = k + base * D, *vb = v + base * D;
 
   float qf[Fr::N];
@@ -236,25 +363,26 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
 #pragma unroll
   for (int c = 0; c < CPL; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   float mx = kLowest, l = 0.f;
-#pragma unroll 1
-  for (uint32_t i0 = 16 * part; i0 < w.n; i0 += 16 * d.split) {
-    int bz, by, bx;
-    w.at(min(i0 + m, w.n - 1), bz, by, bx);
-    const uint32_t p = w.plane(by, bx);
+  walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
+    const uint32_t p = run.pl[16 * ch + m];
     float kf[Fr::N];
-    Fr::load(kb + (int64_t)w.tok(bz, p) * D, g, kf);
-    uint32_t tk[4];
-    bool in[4];
-    w.four(i0 + 4 * g, tk, in);
+    Fr::load(kb + (int64_t)run.tok[16 * ch + m] * D, g, kf);
     float va[4][CPL];
+    typename Fr::Raw vr;
+    if constexpr (X) {
+      Fr::load(vb + (int64_t)run.tok[16 * ch + m] * D, g, vr);
+    } else {
+      const uint4 t4 = *reinterpret_cast<const uint4*>(&run.tok[16 * ch + 4 * g]);
+      const uint32_t tk[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) load_n<T, CPL>(vb + (int64_t)tk[r] * D + m * CPL, va[r]);
+      for (int r = 0; r < 4; ++r) load_n<T, CPL>(vb + (int64_t)tk[r] * D + m * CPL, va[r]);
+    }
     if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, kf);
     if (d.norm) Fr::normalise(kf, d.eps);
     const f32x4 s = contract<Fr::N>(kf, qf);
     float sv[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sv[r] = in[r] ? s[r] : -INFINITY;
+    for (int r = 0; r < 4; ++r) sv[r] = pick(see, r, s[r], -INFINITY);
     // the reference moves only when a score exceeds it by more than 16: weights stay below 2^16
     const float top = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
     if (__any(top > mx + 16.f)) {
@@ -270,17 +398,31 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
       pw[r] = __builtin_amdgcn_exp2f(sv[r] - mx);
       l += pw[r];
     }
+    // not finite: a value of V (a product of its row with zeros shows it)
     float bad = 0.f;
+    if constexpr (X) {
+      wave_lds_fence();  // the last chunk's reads are done
+      to_lds16(tv[wave], m, g, vr.v);
+      typename Fr::Raw zero;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) bad = not_finite<CPL>(va[r], bad);
+      for (int j = 0; j < Fr::NP; ++j) zero.v[j] = make_uint4(0u, 0u, 0u, 0u);
+      const f32x4 z = contract16(vr.v, zero.v);
+      bad = z[0] + z[1] + z[2] + z[3];
+      wave_lds_fence();
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bad = not_finite<CPL>(va[r], bad);
+    }
     if (__any(bad != 0.f)) {
-      add_in_window<CPL>(acc, pw, in, m, g, [&](int j, int r, int e) {
-        return ldf(vb + (int64_t)(uint32_t)__shfl((int)tk[r], 16 * j) * D + e);
+      add_in_window<CPL, X>(acc, pw, see, m, g, [&](int j, int r, int e) {
+        return ldf(vb + (int64_t)run.tok[16 * ch + 4 * j + r] * D + e);
       });
+    } else if constexpr (X) {
+      add_product16<CPL>(acc, tv[wave], m, g, pw);
     } else {
       add_product<CPL>(acc, va, pw);
     }
-  }
+  });
   l = sum_over_rows(l);
   if (d.split > 1) {  // merge the waves of a tile: common reference, then sums
     if (part > 0) {
@@ -307,7 +449,7 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
       }
     }
   }
-  if (!store || !w.live) return;
+  if (!at.store || !w.live) return;
   const float inv = 1.f / l;
   float o[4 * CPL];
   const int64_t row = base + mine;
@@ -318,8 +460,9 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       float x = acc[c][r] * inv;
-      if (gate) x *= gate_dim == 1 ? g1 : 1.f / (1.f + expf(-ldf(gp + CPL * r + c)));
-      o[CPL * r + c] = x;
+      const int e = channel<CPL, X>(0, c, r);
+      if (gate) x *= gate_dim == 1 ? g1 : 1.f / (1.f + expf(-ldf(gp + e)));
+      o[e] = x;
     }
   store_n<T, 4 * CPL>(out + row * D + 4 * CPL * g, o);
   if (lse && g == 0) lse[row] = mx * kLn2 + logf(l);
@@ -388,8 +531,9 @@ __device__ __forceinline__ void merge_waves(f32x4 (&acc)[CPL], float* buf, int s
 }
 
 // ---- dq --------------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(256) na3d_any_dq_kernel(const T* __restrict__ q, const T* __restrict__ k,
+// X: bf16 rows and dO in one term
+template <typename T, int D, bool X>
+__global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                           const T* __restrict__ v, const float2* __restrict__ cs,
                                                           const T* __restrict__ dout, const T* __restrict__ dlo,
                                                           const float* __restrict__ lse, const float* __restrict__ dvec,
@@ -397,14 +541,14 @@ __global__ void __launch_bounds__(256) na3d_any_dq_kernel(const T* __restrict__ 
   using Fr = Frag<T, D>;
   constexpr int CPL = D / 16, LD = D + 4;
   __shared__ __attribute__((aligned(16))) float lds[4 * 16 * LD];
+  __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  int part;
-  bool store;
-  const uint32_t tile = wave_tile(d, wave, part, store);
-  const Walk w = Walk::make<false>(d, tile, m);
-  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = w.bh * n_tok;
+  const Place at = wave_place(d, wave);
+  const int part = at.part;
+  const Walk w = Walk::make<false>(d, at.tile, m);
+  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
   const uint32_t mine = w.mine();
-  const float2* ph = cs ? cs + (int64_t)w.b * d.H * d.W * (D / 2) : nullptr;
+  const float2* ph = cs ? cs + (int64_t)at.b * d.H * d.W * (D / 2) : nullptr;
   const float2* phq = ph ? ph + (int64_t)w.mine_in_plane() * (D / 2) : nullptr;
   const T *kb = k + base * D, *vb = v + base * D;
   const int64_t row = base + mine;
@@ -417,153 +561,179 @@ __global__ void __launch_bounds__(256) na3d_any_dq_kernel(const T* __restrict__ 
   const float qs = d.scale * kLog2e;
 #pragma unroll
   for (int i = 0; i < Fr::N; ++i) qf[i] *= qs;
-  Fr::load(dout + row * D, g, gf);
-  if (dlo) {
-    float lf[Fr::N];
-    Fr::load(dlo + row * D, g, lf);
+  typename Fr::Raw gr;
+  if constexpr (X) {
+    Fr::load(dout + row * D, g, gr);
+  } else {
+    Fr::load(dout + row * D, g, gf);
+    if (dlo) {
+      float lf[Fr::N];
+      Fr::load(dlo + row * D, g, lf);
 #pragma unroll
-    for (int i = 0; i < Fr::N; ++i) gf[i] += lf[i];
+      for (int i = 0; i < Fr::N; ++i) gf[i] += lf[i];
+    }
   }
   const float L = lse[row], Dv = dvec[row];
   f32x4 acc[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (uint32_t i0 = 16 * part; i0 < w.n; i0 += 16 * d.split) {
-    int bz, by, bx;
-    w.at(min(i0 + m, w.n - 1), bz, by, bx);
-    const uint32_t p = w.plane(by, bx), t = w.tok(bz, p);
-    float kf[Fr::N], vf[Fr::N];
+  walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
+    const uint32_t p = run.pl[16 * ch + m], t = run.tok[16 * ch + m];
+    float kf[Fr::N];
     Fr::load(kb + (int64_t)t * D, g, kf);
-    Fr::load(vb + (int64_t)t * D, g, vf);
-    uint32_t tk[4];
-    bool in[4];
-    w.four(i0 + 4 * g, tk, in);
+    f32x4 y;
+    if constexpr (X) {
+      typename Fr::Raw vr;
+      Fr::load(vb + (int64_t)t * D, g, vr);
+      y = contract16(vr.v, gr.v);
+    } else {
+      float vf[Fr::N];
+      Fr::load(vb + (int64_t)t * D, g, vf);
+      y = contract<Fr::N>(vf, gf);
+    }
     if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, kf);
     if (d.norm) Fr::normalise(kf, d.eps);
     wave_lds_fence();  // the last chunk's reads are done
     Fr::to_lds(kt + m * LD, g, kf);
     const f32x4 s = contract<Fr::N>(kf, qf);
-    const f32x4 y = contract<Fr::N>(vf, gf);
     float ds[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float pw = __builtin_amdgcn_exp2f(fmaf(-L, kLog2e, s[r]));
-      ds[r] = in[r] ? pw * (y[r] - Dv) : 0.f;
+      ds[r] = pick(see, r, pw * (y[r] - Dv), 0.f);
     }
     wave_lds_fence();
-    if (__any(not_finite<Fr::N>(kf, 0.f) != 0.f)) {
-      add_in_window<CPL>(acc, ds, in, m, g, [&](int j, int r, int e) { return kt[(4 * j + r) * LD + e]; });
+    // a row of K~ that is not finite makes every score of its row so
+    const float sv[4] = {s[0], s[1], s[2], s[3]};
+    if (__any(not_finite<4>(sv, 0.f) != 0.f)) {
+      add_in_window<CPL, false>(acc, ds, see, m, g, [&](int j, int r, int e) { return kt[(4 * j + r) * LD + e]; });
     } else {
       float ka[4][CPL];
 #pragma unroll
       for (int r = 0; r < 4; ++r) load_n<float, CPL>(kt + (4 * g + r) * LD + m * CPL, ka[r]);
       add_product<CPL>(acc, ka, ds);
     }
-  }
+  });
   if (d.split > 1) {
     __syncthreads();
     merge_waves<CPL>(acc, lds, 16 * LD, wave, part, d.split, lane);
   }
-  if (store) finish_row<T, D>(acc, d.scale, q + row * D, phq, d, g, w.live, dq + row * D);
+  if (at.store) finish_row<T, D>(acc, d.scale, q + row * D, phq, d, g, w.live, dq + row * D);
 }
 
 // ---- dk, dv ----------------------------------------------------------------
-template <typename T, int D>
-__global__ void __launch_bounds__(256) na3d_any_dkdv_kernel(const T* __restrict__ q, const T* __restrict__ k,
+template <typename T, int D, bool X>
+__global__ void __launch_bounds__(256, D == 64 ? 3 : 1) na3d_any_dkdv_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                             const T* __restrict__ v, const float2* __restrict__ cs,
                                                             const T* __restrict__ dout, const T* __restrict__ dlo,
                                                             const float* __restrict__ lse, const float* __restrict__ dvec,
                                                             T* __restrict__ dk, T* __restrict__ dv, AnyDims d) {
   using Fr = Frag<T, D>;
-  constexpr int CPL = D / 16, LD = D + 4, WAVE = 2 * 16 * LD + 32;
+  constexpr int CPL = D / 16, LD = D + 4, GT = X ? 4 * row16(D) : 16 * LD;  // floats of the dO tile
+  constexpr int WAVE = 16 * LD + GT + 32;
   __shared__ __attribute__((aligned(16))) float lds[4 * WAVE];
+  __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  int part;
-  bool store;
-  const uint32_t tile = wave_tile(d, wave, part, store);
-  const Walk w = Walk::make<true>(d, tile, m);
-  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = w.bh * n_tok;
+  const Place at = wave_place(d, wave);
+  const int part = at.part;
+  const Walk w = Walk::make<true>(d, at.tile, m);
+  const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
   const uint32_t mine = w.mine();
-  const float2* ph = cs ? cs + (int64_t)w.b * d.H * d.W * (D / 2) : nullptr;
+  const float2* ph = cs ? cs + (int64_t)at.b * d.H * d.W * (D / 2) : nullptr;
   const float2* phk = ph ? ph + (int64_t)w.mine_in_plane() * (D / 2) : nullptr;
   const T *qb = q + base * D, *gb = dout + base * D, *lb = dlo ? dlo + base * D : nullptr;
   const int64_t row = base + mine;
-  float *qt = lds + wave * WAVE, *gt = qt + 16 * LD, *st = gt + 16 * LD;
+  float *qt = lds + wave * WAVE, *gt = qt + 16 * LD, *st = gt + GT;
 
   float kf[Fr::N], vf[Fr::N];
   Fr::load(k + row * D, g, kf);
   if (phk) Fr::rotate(phk, g, kf);
   if (d.norm) Fr::normalise(kf, d.eps);
-  Fr::load(v + row * D, g, vf);
+  typename Fr::Raw vr;
+  if constexpr (X) Fr::load(v + row * D, g, vr);
+  else Fr::load(v + row * D, g, vf);
   const float qs = d.scale * kLog2e;
   f32x4 ak[CPL], av[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (uint32_t i0 = 16 * part; i0 < w.n; i0 += 16 * d.split) {
-    int bz, by, bx;
-    w.at(min(i0 + m, w.n - 1), bz, by, bx);
-    const uint32_t p = w.plane(by, bx), t = w.tok(bz, p);
+  walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
+    const uint32_t p = run.pl[16 * ch + m], t = run.tok[16 * ch + m];
     float qf[Fr::N], gf[Fr::N];
     Fr::load(qb + (int64_t)t * D, g, qf);
-    Fr::load(gb + (int64_t)t * D, g, gf);
+    typename Fr::Raw gr;
     const float stat = g == 0 ? lse[base + t] : g == 1 ? dvec[base + t] : 0.f;
-    if (lb) {
-      float lf[Fr::N];
-      Fr::load(lb + (int64_t)t * D, g, lf);
+    if constexpr (X) {
+      Fr::load(gb + (int64_t)t * D, g, gr);
+    } else {
+      Fr::load(gb + (int64_t)t * D, g, gf);
+      if (lb) {
+        float lf[Fr::N];
+        Fr::load(lb + (int64_t)t * D, g, lf);
 #pragma unroll
-      for (int i = 0; i < Fr::N; ++i) gf[i] += lf[i];
+        for (int i = 0; i < Fr::N; ++i) gf[i] += lf[i];
+      }
     }
-    uint32_t tk[4];
-    bool in[4];
-    w.four(i0 + 4 * g, tk, in);
     if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, qf);
     if (d.norm) Fr::normalise(qf, d.eps);
-#pragma unroll
-    for (int i = 0; i < Fr::N; ++i) qf[i] *= qs;
     wave_lds_fence();  // the last chunk's reads are done
     Fr::to_lds(qt + m * LD, g, qf);
-    Fr::to_lds(gt + m * LD, g, gf);
+    f32x4 y;
+    if constexpr (X) {
+      to_lds16(reinterpret_cast<char*>(gt), m, g, gr.v);
+      y = contract16(gr.v, vr.v);
+    } else {
+      Fr::to_lds(gt + m * LD, g, gf);
+      y = contract<Fr::N>(gf, vf);
+    }
     if (g < 2) st[lane] = stat;
     const f32x4 s = contract<Fr::N>(qf, kf);
-    const f32x4 y = contract<Fr::N>(gf, vf);
     wave_lds_fence();
     const float4 L = *reinterpret_cast<const float4*>(st + 4 * g), Dv = *reinterpret_cast<const float4*>(st + 16 + 4 * g);
     const float Ls[4] = {L.x, L.y, L.z, L.w}, Ds[4] = {Dv.x, Dv.y, Dv.z, Dv.w};
     float pw[4], ds[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      pw[r] = in[r] ? __builtin_amdgcn_exp2f(fmaf(-Ls[r], kLog2e, s[r])) : 0.f;
-      ds[r] = in[r] ? pw[r] * (y[r] - Ds[r]) : 0.f;
+      pw[r] = pick(see, r, __builtin_amdgcn_exp2f(fmaf(s[r], qs, -kLog2e * Ls[r])), 0.f);
+      ds[r] = pick(see, r, pw[r] * (y[r] - Ds[r]), 0.f);
     }
-    if (__any(not_finite<Fr::N>(qf, not_finite<Fr::N>(gf, 0.f)) != 0.f)) {
-      add_in_window<CPL>(av, pw, in, m, g, [&](int j, int r, int e) { return gt[(4 * j + r) * LD + e]; });
-      add_in_window<CPL>(ak, ds, in, m, g, [&](int j, int r, int e) { return qt[(4 * j + r) * LD + e]; });
+    // a row of Q~ or dO that is not finite makes every score or product of its row so
+    const float sy[8] = {s[0], s[1], s[2], s[3], y[0], y[1], y[2], y[3]};
+    if (__any(not_finite<8>(sy, 0.f) != 0.f)) {
+      add_in_window<CPL, X>(av, pw, see, m, g, [&](int j, int r, int e) {
+        if constexpr (X)
+          return ldf(reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(gt) + (4 * j + r) * row16(D)) + e);
+        else
+          return gt[(4 * j + r) * LD + e];
+      });
+      add_in_window<CPL, false>(ak, ds, see, m, g, [&](int j, int r, int e) { return qt[(4 * j + r) * LD + e]; });
     } else {
       float a[4][CPL];
+      if constexpr (X) {
+        add_product16<CPL>(av, reinterpret_cast<const char*>(gt), m, g, pw);
+      } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) load_n<float, CPL>(gt + (4 * g + r) * LD + m * CPL, a[r]);
-      add_product<CPL>(av, a, pw);
+        for (int r = 0; r < 4; ++r) load_n<float, CPL>(gt + (4 * g + r) * LD + m * CPL, a[r]);
+        add_product<CPL>(av, a, pw);
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) load_n<float, CPL>(qt + (4 * g + r) * LD + m * CPL, a[r]);
       add_product<CPL>(ak, a, ds);
     }
-  }
+  });
   if (d.split > 1) {
     __syncthreads();
     merge_waves<CPL>(ak, lds, WAVE, wave, part, d.split, lane);
-    merge_waves<CPL>(av, lds + 16 * LD, WAVE, wave, part, d.split, lane);
+    __syncthreads();
+    merge_waves<CPL>(av, lds, WAVE, wave, part, d.split, lane);
   }
-  if (!store) return;
-  // the staged queries carry scale log2(e)
-  finish_row<T, D>(ak, kLn2, k + row * D, phk, d, g, w.live, dk + row * D);
+  if (!at.store) return;
+  finish_row<T, D>(ak, d.scale, k + row * D, phk, d, g, w.live, dk + row * D);
   if (w.live) {
     float o[4 * CPL];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) o[CPL * r + c] = av[c][r];
+      for (int c = 0; c < CPL; ++c) o[channel<CPL, X>(0, c, r)] = av[c][r];
     store_n<T, 4 * CPL>(dv + row * D + 4 * CPL * g, o);
   }
 }
@@ -593,10 +763,7 @@ __global__ void __launch_bounds__(256) na3d_bwd_pre_kernel(const T* __restrict__
   if (row < nq && c == 0) dvec[row] = acc;
 }
 
-dim3 any_grid(const AnyDims& a) {
-  const int per = 4 / a.split;
-  return dim3((uint32_t)((a.tiles + per - 1) / per));
-}
+dim3 any_grid(const AnyDims& a) { return dim3((uint32_t)any_blocks(a)); }
 
 template <typename T, int D>
 void fwd_any(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k, const void* v, const float* cs,
@@ -619,14 +786,19 @@ void bwd_any(int part, const strata_na3d_desc& d, const BwdOpts& o, const void* 
     return;
   }
   const AnyDims a = any_dims(d.B, d.heads, d.Z, d.H, d.W, d.kz, d.ky, d.kx, d.scale, o.qk_norm, o.eps);
-  if (part == 1)
-    hipLaunchKernelGGL((na3d_any_dq_kernel<T, D>), any_grid(a), dim3(256), 0, s, static_cast<const T*>(q),
-                       static_cast<const T*>(k), static_cast<const T*>(v), c2, static_cast<const T*>(dout),
-                       static_cast<const T*>(o.dout_lo), lse, dvec, static_cast<T*>(dq), a);
-  else
-    hipLaunchKernelGGL((na3d_any_dkdv_kernel<T, D>), any_grid(a), dim3(256), 0, s, static_cast<const T*>(q),
-                       static_cast<const T*>(k), static_cast<const T*>(v), c2, static_cast<const T*>(dout),
-                       static_cast<const T*>(o.dout_lo), lse, dvec, static_cast<T*>(dk), static_cast<T*>(dv), a);
+  const bool x = sizeof(T) == 2 && !o.dout_lo;
+#define STRATA_ANY(K, XX, ...)                                                                                       \
+  hipLaunchKernelGGL((K<T, D, XX>), any_grid(a), dim3(256), 0, s, static_cast<const T*>(q), static_cast<const T*>(k), \
+                     static_cast<const T*>(v), c2, static_cast<const T*>(dout), static_cast<const T*>(o.dout_lo), lse, \
+                     dvec, __VA_ARGS__, a)
+  if (part == 1) {
+    if (x) STRATA_ANY(na3d_any_dq_kernel, sizeof(T) == 2, static_cast<T*>(dq));
+    else STRATA_ANY(na3d_any_dq_kernel, false, static_cast<T*>(dq));
+  } else {
+    if (x) STRATA_ANY(na3d_any_dkdv_kernel, sizeof(T) == 2, static_cast<T*>(dk), static_cast<T*>(dv));
+    else STRATA_ANY(na3d_any_dkdv_kernel, false, static_cast<T*>(dk), static_cast<T*>(dv));
+  }
+#undef STRATA_ANY
 }
 
 }  // namespace

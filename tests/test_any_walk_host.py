@@ -6,8 +6,8 @@ with either parity, columns, single positions, extents that the tile does not
 divide): the tiles' live tokens cover the grid once; the chunks of every tile
 stay inside the grid and show each lane exactly the tokens of its
 border-clamped window (Sec. 3.2), or the queries whose window holds it, once
-each, by brute force over the definition; and the division by a fixed number
-is exact up to 2^30.
+each, by brute force over the definition; every (batch, head) gets a wave; and
+the division by a fixed number is exact up to 2^30.
 """
 import os
 import shutil
@@ -23,6 +23,7 @@ HARNESS = r"""
 #define __device__
 #define __forceinline__ inline
 #include <algorithm>
+#include <cstdint>
 #include <cstdio>
 #include <random>
 #include <vector>
@@ -40,39 +41,42 @@ static bool holds(int q, int j, int L, int k) { const int s = begin_of(q, L, k);
 template <bool INV>
 static int check(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
   const AnyDims d = any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f);
-  const int N = Z * H * W;
-  std::vector<int> cover((size_t)B * heads * N, 0);
-  for (int64_t t = 0; t < d.tiles; ++t)
+  const int N = Z * H * W, per = 4 / d.split;
+  if (d.nbh != (uint32_t)(B * heads) || any_blocks(d) != (int64_t)d.places.n * ((B * heads + per - 1) / per)) return printf("blocks\n"), 1;
+  std::vector<int> cover(N, 0);
+  static Run run;
+  for (uint32_t t = 0; t < d.places.n; ++t) {
+    std::vector<Walk> w;
     for (int m = 0; m < 16; ++m) {
-      const Walk w = Walk::make<INV>(d, (uint32_t)t, m);
-      if (w.bh < 0 || w.bh >= (int64_t)B * heads || w.b != w.bh / heads) return printf("tile index\n"), 1;
-      if (w.z < 0 || w.z >= Z || w.y < 0 || w.y >= H || w.x < 0 || w.x >= W) return printf("token outside\n"), 1;
-      if (w.live) cover[w.bh * N + w.mine()]++;
-      if (t > 40 && t % 7) continue;  // the walk of a part of the tiles
-      std::vector<int> seen(N, 0);
-      for (uint32_t i0 = 0; i0 < w.n; i0 += 16) {
-        int bz, by, bx;
-        w.at(min(i0 + m, w.n - 1), bz, by, bx);
-        const uint32_t own = w.tok(bz, w.plane(by, bx));
-        for (int g = 0; g < 4; ++g) {
-          uint32_t tk[4];
-          bool in[4];
-          w.four(i0 + 4 * g, tk, in);
+      w.push_back(Walk::make<INV>(d, t, m));
+      const Walk& a = w.back();
+      if (a.z < 0 || a.z >= Z || a.y < 0 || a.y >= H || a.x < 0 || a.x >= W) return printf("token outside\n"), 1;
+      if (a.live) cover[a.mine()]++;
+      if (a.mine() != (uint32_t)((a.z * H + a.y) * W + a.x) || a.n != w[0].n) return printf("tile\n"), 1;
+    }
+    if (t > 40 && t % 7) continue;  // the walk of a part of the tiles
+    std::vector<int> seen(16 * N, 0);
+    for (uint32_t i0 = 0; i0 < w[0].n; i0 += 16 * kRun) {
+      for (int j = 0; j < 16 * kRun; ++j) run.tok[j] = run.pl[j] = ~0u;
+      for (int tid = 0; tid < 256; ++tid) fill_run(w[tid & 15], run, i0, tid);
+      for (uint32_t c = 0; c < min((uint32_t)kRun, (w[0].n - i0 + 15) / 16); ++c)
+        for (int lane = 0; lane < 64; ++lane)
           for (int r = 0; r < 4; ++r) {
-            if (tk[r] >= (uint32_t)N) return printf("token %u of %d\n", tk[r], N), 1;
-            if (in[r]) seen[tk[r]]++;
-            if (4 * g + r == m && tk[r] != own) return printf("row and column disagree\n"), 1;
+            const int j = 16 * c + 4 * (lane >> 4) + r;
+            if (run.tok[j] >= (uint32_t)N || run.pl[j] != run.tok[j] % (uint32_t)(H * W)) return printf("token %u of %d\n", run.tok[j], N), 1;
+            if (run.see[64 * c + lane] >> r & 1) seen[(lane & 15) * N + run.tok[j]]++;
           }
-        }
-      }
+    }
+    for (int m = 0; m < 16; ++m)
       for (int z = 0; z < Z; ++z)
         for (int y = 0; y < H; ++y)
           for (int x = 0; x < W; ++x) {
-            const bool want = INV ? holds(z, w.z, Z, kz) && holds(y, w.y, H, ky) && holds(x, w.x, W, kx)
-                                  : holds(w.z, z, Z, kz) && holds(w.y, y, H, ky) && holds(w.x, x, W, kx);
-            if (seen[(z * H + y) * W + x] != (want ? 1 : 0)) return printf("window of tile %d lane %d\n", (int)t, m), 1;
+            const Walk& a = w[m];
+            const bool want = INV ? holds(z, a.z, Z, kz) && holds(y, a.y, H, ky) && holds(x, a.x, W, kx)
+                                  : holds(a.z, z, Z, kz) && holds(a.y, y, H, ky) && holds(a.x, x, W, kx);
+            if (seen[m * N + (z * H + y) * W + x] != (want ? 1 : 0)) return printf("window of tile %d lane %d\n", (int)t, m), 1;
           }
-    }
+  }
   for (int c : cover)
     if (c != 1) return printf("a token in %d tiles\n", c), 1;
   return 0;
@@ -102,7 +106,12 @@ int main() {
     for (uint32_t i : {0u, n - 1, n, (uint32_t)(rng() >> 2), q * n - 1, q * n, (1u << 30) - 1})
       if (i < (1u << 30) && f.div(i) != i / n) return printf("%u / %u = %u\n", i, n, f.div(i)), 1;
   }
-  if (any_fits(1, 1, 1 << 12, 1 << 12, 1 << 12, 3, 3, 3) || !any_fits(81, 16, 24, 512, 512, 9, 9, 9)) return printf("fits\n"), 1;
+  for (int bh = 1; bh < 400; ++bh) {  // every grid has a wave, few waves have none
+    const AnyDims d = any_dims(1, bh, 5, 9, 9, 3, 3, 3, 1.f, 0, 0.f);
+    const int per = 4 / d.split, groups = (bh + per - 1) / per;
+    if (groups * per < bh || groups * per > bh * 1.15 + 1e-9) return printf("%d grids: %d x %d\n", bh, groups, per), 1;
+  }
+  if (any_fits(1, 1, 1 << 12, 1 << 12, 1 << 12, 3, 3, 3) || !any_fits(81, 16, 24, 128, 128, 9, 9, 9) || !any_fits(1 << 13, 1 << 13, 1, 1, 1, 1, 1, 1)) return printf("fits\n"), 1;
   printf("ok\n");
   return 0;
 }
