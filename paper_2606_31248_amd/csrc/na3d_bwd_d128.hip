@@ -8,9 +8,13 @@
 //
 // The same two passes and arithmetic as at head_dim 64, with 128-wide rows:
 //
-// dQ (query-stationary; an 8 x 8 block of (y, x) queries and ZQ levels per
-// workgroup, a 4 x 4 sub-block on all ZQ levels per wave, one wave per SIMD
-// so that the S/Y chunks, dO and Q of a level fit in its registers).  Per (query level, key level):
+// dQ (query-stationary; an 8 x 8 block of (y, x) queries on two levels per
+// workgroup, eight waves: a 4 x 4 sub-block on one level each).  A staged key
+// level serves both query levels, and the two waves of a SIMD hide each other's
+// LDS reads; the keys are taken 32 at a time, so that no level's scores are held
+// at once.  Decoder shape (24x64x64, one head, QK norm, gate per channel): 0.66 ms
+// with four waves, one per SIMD, each holding a whole level's scores and staging
+// a key level for one query level, 0.34 ms now.  Per (query level, key level):
 //   S^T = K~ . Q~^T             four float16 MFMAs per 16-key chunk, seeded
 //                               with the window mask; P^T = exp2(S^T - LSE)
 //                               from the forward's log-sum-exp;
@@ -77,12 +81,12 @@ struct Args {
 
 // ============================================================================ dQ
 constexpr int kQBY = 8, kQBX = 8;
-constexpr int kQWaves = 4, kQThreads = 64 * kQWaves;  // one wave per SIMD: up to 512 registers each
-constexpr int kQGroups = kQWaves / 4;                 // level groups (waves 4g..4g+3 take levels = g mod kQGroups)
 constexpr int kKRow = 256, kVRow = 288;
 
-template <int KZ, int KY, int KX, int ZQ>
+// NG groups of four waves; waves 4 grp .. 4 grp + 3 take the query levels grp + NG j, j < QL
+template <int KZ, int KY, int KX, int NG, int QL_>
 struct QCfg {
+  static constexpr int QL = QL_, ZQ = NG * QL, kQThreads = 256 * NG;
   static constexpr int LY = kQBY + KY - 1, LX = kQBX + KX - 1;
   static constexpr int NUY = 3 + KY, NUX = 3 + KX, NU = NUY * NUX;
   static constexpr int NC = (NU + 15) / 16, NS = (NC + 1) / 2;
@@ -91,14 +95,14 @@ struct QCfg {
   static constexpr int KBYTES = KEYS * kKRow, VBYTES = KEYS * kVRow;
   static constexpr int ITK = (KSLOTS + kQThreads - 1) / kQThreads;
   static constexpr int ITV = (VSLOTS + kQThreads - 1) / kQThreads;
-  static constexpr int QL = ZQ / kQGroups;
-  static_assert(ZQ % kQGroups == 0 && NC <= 16, "layout");
+  static_assert(NC <= 16, "layout");
   static_assert(KBYTES + VBYTES <= kLdsMax, "key tiles exceed LDS");
 };
 
-template <int KZ, int KY, int KX, int ZQ, bool NORM, bool LO>
-__global__ void __launch_bounds__(kQThreads, 1) na3d_bwd_dq_d128_kernel(Args a) {
-  using C = QCfg<KZ, KY, KX, ZQ>;
+template <int KZ, int KY, int KX, int NG, int QL, bool NORM, bool LO>
+__global__ void __launch_bounds__(256 * NG, 1) na3d_bwd_dq_d128_kernel(Args a) {
+  using C = QCfg<KZ, KY, KX, NG, QL>;
+  constexpr int kQThreads = C::kQThreads, ZQ = C::ZQ;
   __shared__ __attribute__((aligned(16))) char tK[C::KBYTES];
   __shared__ __attribute__((aligned(16))) char tV[C::VBYTES];
 
@@ -216,7 +220,7 @@ __global__ void __launch_bounds__(kQThreads, 1) na3d_bwd_dq_d128_kernel(Args a) 
   const float4* csq = csb ? csb + ((int64_t)qy * W + qx) * kCS4 : nullptr;
 #pragma unroll
   for (int j = 0; j < C::QL; ++j) {
-    const int zq = min(z0 + grp + kQGroups * j, Z - 1);
+    const int zq = min(z0 + grp + NG * j, Z - 1);
     const int64_t tok = bh_base + zq * HW + (int64_t)qy * W + qx;
     const uint4* src = reinterpret_cast<const uint4*>(a.q + tok * kD);
     const uint4* gsrc = reinterpret_cast<const uint4*>(a.dout + tok * kD);
@@ -245,59 +249,81 @@ __global__ void __launch_bounds__(kQThreads, 1) na3d_bwd_dq_d128_kernel(Args a) 
     for (int t = 0; t < 8; ++t) o[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  auto update_dq = [&](int j) {
-    // dS = P Y per chunk in float32 (P = exp2(S^T - LSE) <= 1), and the bound of |Y|
-    f32x4 ds[C::NC];
-    float my = 0.f;
+  // the keys 32 at a time (two chunks): scores and Y, the bound of |Y| grown to
+  // cover them, dS and the step's dQ MFMAs
+  auto update_dq = [&](int j) __attribute__((always_inline)) {
+    // the mask bits pass through an empty asm, so that the seeds are derived
+    // step by step instead of kept in registers
+    uint32_t mw[2] = {(uint32_t)mbits, (uint32_t)(mbits >> 32)};
+    asm volatile("" : "+v"(mw[0]), "+v"(mw[1]));
     const f32x4 ndv = {nd[j], nd[j], nd[j], nd[j]};
 #pragma unroll
-    for (int c = 0; c < C::NC; ++c) {
-      f32x4 acc;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = ((mbits >> (4 * c + i)) & 1ull) ? 0.f : -INFINITY;
-      f32x4 yy = ndv;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const f16x8 kf = __builtin_bit_cast(f16x8, ld16(tK + (kaddr[c] ^ (64u * kk))));
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[j][kk], acc, 0, 0, 0);
-        const bf16x8 vv = __builtin_bit_cast(bf16x8, ld16(tV + vrow[c] + 64 * kk));
-        yy = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, gf[j][kk], yy, 0, 0, 0);
-        if constexpr (LO) yy = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, gl[j][kk], yy, 0, 0, 0);
-      }
-      my = fmaxf(fmaxf(my, fmaxf(fabsf(yy[0]), fabsf(yy[1]))), fmaxf(fabsf(yy[2]), fabsf(yy[3])));
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ds[c][i] = __builtin_amdgcn_exp2f(acc[i] - lse2[j]) * yy[i];
-    }
-    my = max_over_rows(my);
-    const int e = max(__builtin_amdgcn_frexp_expf(my), kMinExp);
-    if (__any(e > ex[j])) {  // the bound grew: rescale the accumulator exactly
-      const int en = max(ex[j], e);
-      const float f = __builtin_amdgcn_ldexpf(1.f, ex[j] - en);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) o[j][t] *= f;
-      ex[j] = en;
-    }
-    const float sc = __builtin_amdgcn_ldexpf(1.f, 15 - ex[j]);  // |dS| 2^(15-E) < 2^15
-    uint32_t dk[C::NC][2];
-#pragma unroll
-    for (int c = 0; c < C::NC; ++c) {
-      dk[c][0] = pack2h_rne(ds[c][0] * sc, ds[c][1] * sc);
-      dk[c][1] = pack2h_rne(ds[c][2] * sc, ds[c][3] * sc);
-    }
-#pragma unroll
     for (int st = 0; st < C::NS; ++st) {
-      const int c0 = 2 * st, c1 = 2 * st + 1;
-      const bool two = c1 < C::NC;
-      const int cc = two ? c1 : c0;
-      const f16x8 df = __builtin_bit_cast(f16x8, make_uint4(dk[c0][0], dk[c0][1], two ? dk[cc][0] : 0u, two ? dk[cc][1] : 0u));
+      f32x4 x[2], y[2];
+      float my = 0.f;
+      uint32_t ka[2], kta[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = 2 * st + h < C::NC ? 2 * st + h : C::NC - 1;
+        ka[h] = kaddr[c];
+        kta[h] = ktaddr[c];
+        asm volatile("" : "+v"(ka[h]), "+v"(kta[h]));
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = 2 * st + h;
+        if (c >= C::NC) {
+          x[h] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+          y[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+          continue;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // 0 where the query sees the key, else -inf
+          const int bit = 4 * c + i;
+          const uint32_t sel = (uint32_t)__builtin_amdgcn_sbfe((int)mw[bit >> 5], bit & 31, 1);
+          x[h][i] = __uint_as_float(~sel & 0xff800000u);
+        }
+        y[h] = ndv;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const f16x8 kf = __builtin_bit_cast(f16x8, ld16(tK + (ka[h] ^ (64u * kk))));
+          x[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[j][kk], x[h], 0, 0, 0);
+          const bf16x8 vv = __builtin_bit_cast(bf16x8, ld16(tV + vrow[c] + 64 * kk));
+          y[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, gf[j][kk], y[h], 0, 0, 0);
+          if constexpr (LO) y[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, gl[j][kk], y[h], 0, 0, 0);
+        }
+        my = fmaxf(fmaxf(my, fmaxf(fabsf(y[h][0]), fabsf(y[h][1]))), fmaxf(fabsf(y[h][2]), fabsf(y[h][3])));
+      }
+      my = max_over_rows(my);
+      const int e = max(__builtin_amdgcn_frexp_expf(my), kMinExp);
+      if (__any(e > ex[j])) {  // the bound grew: rescale the accumulator exactly
+        const int en = max(ex[j], e);
+        const float f = __builtin_amdgcn_ldexpf(1.f, ex[j] - en);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) o[j][t] *= f;
+        ex[j] = en;
+      }
+      const float sc = __builtin_amdgcn_ldexpf(1.f, 15 - ex[j]);  // |dS| 2^(15-E) < 2^15
+      uint32_t dk[2][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float ds[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ds[i] = __builtin_amdgcn_exp2f(x[h][i] - lse2[j]) * y[h][i] * sc;
+        dk[h][0] = pack2h_rne(ds[0], ds[1]);
+        dk[h][1] = pack2h_rne(ds[2], ds[3]);
+      }
+      const f16x8 df = __builtin_bit_cast(f16x8, make_uint4(dk[0][0], dk[0][1], dk[1][0], dk[1][1]));
+      const bool two = 2 * st + 1 < C::NC;
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
-        const i16x4 lo = tr_read(tK + (ktaddr[c0] ^ (32u * t)));
-        const i16x4 hi = two ? tr_read(tK + (ktaddr[cc] ^ (32u * t))) : i16x4{0, 0, 0, 0};
+        const i16x4 lo = tr_read(tK + (kta[0] ^ (32u * t)));
+        const i16x4 hi = two ? tr_read(tK + (kta[1] ^ (32u * t))) : i16x4{0, 0, 0, 0};
         const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
         const f16x8 kt = __builtin_bit_cast(f16x8, make_uint4(l2.x, l2.y, h2.x, h2.y));
         o[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kt, df, o[j][t], 0, 0, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);  // keep the next step's loads out of this one's registers
     }
   };
 
@@ -311,7 +337,7 @@ __global__ void __launch_bounds__(kQThreads, 1) na3d_bwd_dq_d128_kernel(Args a) 
     __syncthreads();  // the level is published
 #pragma unroll
     for (int j = 0; j < C::QL; ++j) {
-      const int zq = z0 + grp + kQGroups * j;
+      const int zq = z0 + grp + NG * j;
       if (zq >= Z) continue;
       const int zs = win_start(zq, Z, KZ);
       if (p < zs || p >= zs + KZ) continue;
@@ -324,7 +350,7 @@ __global__ void __launch_bounds__(kQThreads, 1) na3d_bwd_dq_d128_kernel(Args a) 
   const bool in_grid = qy_raw < H && qx_raw < W;
 #pragma unroll
   for (int j = 0; j < C::QL; ++j) {
-    const int zq = z0 + grp + kQGroups * j;
+    const int zq = z0 + grp + NG * j;
     if (zq >= Z || !in_grid) continue;
     const float f = a.scale * __builtin_amdgcn_ldexpf(1.f, ex[j] - 15);
     const int64_t tok = bh_base + zq * HW + (int64_t)qy * W + qx;
@@ -761,23 +787,23 @@ bool launch_na3d_bwd_dq_d128(const strata_na3d_desc& d, const BwdOpts& o, const 
   a.dq = static_cast<uint16_t*>(dq);
   a.eps = o.eps;
   a.dout_lo = static_cast<const uint16_t*>(o.dout_lo);
-  // two query levels per wave, one with the two-term dO (its low term's
-  // fragments would not fit beside two levels' state)
-  const int zq = o.dout_lo ? 1 : 2;
+  // two groups of four waves on two query levels (two waves per SIMD, 205-223
+  // registers); three groups would have 168 registers and spill 13-32 of them
+  constexpr int NG = 2, QL = 1, zq = NG * QL;
   a.n_zb = (d.Z + zq - 1) / zq;
   a.n_yb = (d.H + kQBY - 1) / kQBY;
   a.n_xb = (d.W + kQBX - 1) / kQBX;
   const int64_t blocks = (int64_t)d.B * d.heads * a.n_zb * a.n_yb * a.n_xb;
   if (blocks >= (int64_t)1 << 31) return false;
-  const dim3 grid((unsigned)blocks), block(kQThreads);
+  const dim3 grid((unsigned)blocks), block(256 * NG);
   if (o.qk_norm && o.dout_lo)
-    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, 1, true, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, NG, QL, true, true>), grid, block, 0, s, a);
   else if (o.qk_norm)
-    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, 2, true, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, NG, QL, true, false>), grid, block, 0, s, a);
   else if (o.dout_lo)
-    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, 1, false, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, NG, QL, false, true>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, 2, false, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((na3d_bwd_dq_d128_kernel<9, 9, 9, NG, QL, false, false>), grid, block, 0, s, a);
   return true;
 }
 
