@@ -23,15 +23,19 @@
 // the rows, which is the operand layout of the second product as it stands; its
 // other operand holds, for token 4g + r, the head_dim / 16 channels from
 // m head_dim / 16 on, so that output tile c, row m is channel m head_dim / 16 + c.
-// In the backward the staged rows are needed in both layouts: the wave writes
-// them to its own part of LDS and reads them back the other way.
+// A chunk's rows are loaded with four neighbouring lanes to a row (64 bytes
+// together; in the operand layout neighbouring lanes hold different rows, every
+// lane its own access, and the vector cache's access rate bounded the kernels),
+// rotated and normalised there, and pass through the wave's own part of LDS into
+// the operand layout, in the backward also into the other one.
 //
 // Measured against one thread per query (or one wave per query below 2^18) with
 // float32 vector arithmetic: float32 forward and backward, 4 heads x 7x21x27,
-// d 64, 5x9x9: 14733 -> 250 us; bf16 3x3x3 forward and backward, 6 tiles x 16
-// heads x 24x16x16: 20589 -> 868 us (1104 us with each wave forming its own
-// positions and masks, 1015 us with every product in float32); float32 forward,
-// 4 heads x 4x16x16, d 32, 3x7x7: 56.8 -> 13.8 us.
+// d 64, 5x9x9: 14733 -> 212 us; bf16 3x3x3 forward and backward, 6 tiles x 16
+// heads x 24x16x16: 20589 -> 753 us (1104 us with each wave forming its own
+// positions and masks, 1015 us with every product in float32, 868 us with rows
+// loaded in the operand layout); float32 forward,
+// 4 heads x 4x16x16, d 32, 3x7x7: 56.8 -> 9.0 us.
 //
 // Values outside a query's window never reach its results, infinities and NaN
 // included: scores and weights are selected, and a chunk that holds a value that
@@ -109,6 +113,13 @@ __device__ __forceinline__ void store_n(T* p, const float* f) {
   }
 }
 
+// Sum over each aligned group of four lanes
+__device__ __forceinline__ float sum_over_quad(float x) {
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, false));  // quad_perm 1,0,3,2
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, false));  // quad_perm 2,3,0,1
+  return x;
+}
+
 // The lane's share of a row in the operand layout: pieces g, g + 4, ... of 16 bytes
 template <typename T, int D>
 struct Frag {
@@ -163,14 +174,24 @@ struct Frag {
         x[3] = fmaf(c, p.w, d * p.z);
       }
   }
-  // QK RMSNorm: divide the row (its four lanes together) by its root mean square
+  // QK RMSNorm: divide the row by its root mean square, its four lanes together
+  // (QUAD: they are neighbours, the loading layout; else 16 lanes apart)
+  template <bool QUAD>
   static __device__ __forceinline__ void normalise(float* f, float eps) {
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i) ss = fmaf(f[i], f[i], ss);
-    const float r = 1.f / sqrtf(sum_over_rows(ss) / D + eps);
+    const float x = (QUAD ? sum_over_quad(ss) : sum_over_rows(ss)) * (1.f / D) + eps;
+    // within an ulp like the division by the root, which takes the ends of the
+    // range (and 20 more instructions)
+    float r = __builtin_amdgcn_rsqf(x);
+    if (__any(!(x > 1e-30f && x < 1e30f))) r = 1.f / sqrtf(x);
 #pragma unroll
     for (int i = 0; i < N; ++i) f[i] *= r;
+  }
+  static __device__ __forceinline__ void from_lds(const float* row, int g, float* f) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j) load_n<float, E>(row + (4 * j + g) * E, f + j * E);
   }
   static __device__ __forceinline__ void to_lds(float* row, int g, const float* f) {
 #pragma unroll
@@ -216,11 +237,16 @@ __device__ __forceinline__ f32x4 contract16(const uint4 (&a)[NP], const uint4 (&
 // bytes of a staged bf16 row
 constexpr int row16(int D) { return 2 * D + 16; }
 
-// the lane's pieces of row m of a chunk, to its wave's tile of bf16 rows
+// the lane's pieces of row m of a chunk, to and from its wave's tile of bf16 rows
 template <int NP>
 __device__ __forceinline__ void to_lds16(char* tile, int m, int g, const uint4 (&r)[NP]) {
 #pragma unroll
   for (int j = 0; j < NP; ++j) mfma::st16(tile + m * row16(32 * NP) + 16 * (4 * j + g), r[j]);
+}
+template <int NP>
+__device__ __forceinline__ void from_lds16(const char* tile, int m, int g, uint4 (&r)[NP]) {
+#pragma unroll
+  for (int j = 0; j < NP; ++j) r[j] = mfma::ld16(tile + m * row16(32 * NP) + 16 * (4 * j + g));
 }
 
 // acc += rows^T w, rows: the wave's tile of bf16 rows, read transposed (tile c,
@@ -332,17 +358,20 @@ __device__ __forceinline__ float pick(uint32_t see, int r, float x, float other)
 
 // ---- forward ---------------------------------------------------------------
 template <typename T, int D>
-__global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k,
+__global__ void __launch_bounds__(256, D == 64 && sizeof(T) == 2 ? 4 : 1) na3d_any_fwd_kernel(const T* __restrict__ q, const T* __restrict__ k,
                                                            const T* __restrict__ v, const float2* __restrict__ cs,
                                                            T* __restrict__ out, float* __restrict__ lse, AnyDims d,
                                                            const T* __restrict__ gate, int gate_dim) {
   using Fr = Frag<T, D>;
   constexpr bool X = sizeof(T) == 2;
   constexpr int CPL = D / 16, NS = 4 * CPL + 2;
-  __shared__ float merge[3 * 64 * NS];
-  __shared__ __attribute__((aligned(16))) char tv[4][X ? 16 * row16(D) : 16];
+  constexpr int LD = D + 4, KB = 16 * LD * 4, WAVE = KB + (X ? 16 * row16(D) : 0);  // K~ rows, bf16 V rows
+  static_assert(4 * WAVE >= 3 * 64 * NS * 4, "the merge of the waves fits the tiles");
+  __shared__ __attribute__((aligned(16))) char tiles[4 * WAVE];
+  float* const merge = reinterpret_cast<float*>(tiles);
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
   const Place at = wave_place(d, wave);
   const int part = at.part;
   const Walk w = Walk::make<false>(d, at.tile, m);
@@ -354,7 +383,7 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
   float qf[Fr::N];
   Fr::load(q + (base + mine) * D, g, qf);
   if (ph) Fr::rotate(ph + (int64_t)w.mine_in_plane() * (D / 2), g, qf);
-  if (d.norm) Fr::normalise(qf, d.eps);
+  if (d.norm) Fr::template normalise<false>(qf, d.eps);
   const float qs = d.scale * kLog2e;
 #pragma unroll
   for (int i = 0; i < Fr::N; ++i) qf[i] *= qs;
@@ -364,21 +393,27 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
   for (int c = 0; c < CPL; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   float mx = kLowest, l = 0.f;
   walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
-    const uint32_t p = run.pl[16 * ch + m];
+    float* const kt = reinterpret_cast<float*>(tiles + wave * WAVE);
+    char* const tv = tiles + wave * WAVE + KB;
     float kf[Fr::N];
-    Fr::load(kb + (int64_t)run.tok[16 * ch + m] * D, g, kf);
+    Fr::load(kb + (int64_t)run.tok[16 * ch + lm] * D, lg, kf);
     float va[4][CPL];
     typename Fr::Raw vr;
     if constexpr (X) {
-      Fr::load(vb + (int64_t)run.tok[16 * ch + m] * D, g, vr);
+      Fr::load(vb + (int64_t)run.tok[16 * ch + lm] * D, lg, vr);
     } else {
       const uint4 t4 = *reinterpret_cast<const uint4*>(&run.tok[16 * ch + 4 * g]);
       const uint32_t tk[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
       for (int r = 0; r < 4; ++r) load_n<T, CPL>(vb + (int64_t)tk[r] * D + m * CPL, va[r]);
     }
-    if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, kf);
-    if (d.norm) Fr::normalise(kf, d.eps);
+    if (ph) Fr::rotate(ph + (int64_t)run.pl[16 * ch + lm] * (D / 2), lg, kf);
+    if (d.norm) Fr::template normalise<true>(kf, d.eps);
+    wave_lds_fence();  // the last chunk's reads are done
+    Fr::to_lds(kt + lm * LD, lg, kf);
+    if constexpr (X) to_lds16(tv, lm, lg, vr.v);
+    wave_lds_fence();
+    Fr::from_lds(kt + m * LD, g, kf);
     const f32x4 s = contract<Fr::N>(kf, qf);
     float sv[4];
 #pragma unroll
@@ -400,15 +435,12 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
     }
     // not finite: a value of V (a product of its row with zeros shows it)
     float bad = 0.f;
-    if constexpr (X) {
-      wave_lds_fence();  // the last chunk's reads are done
-      to_lds16(tv[wave], m, g, vr.v);
+    if constexpr (X) {  // (whichever lanes hold it)
       typename Fr::Raw zero;
 #pragma unroll
       for (int j = 0; j < Fr::NP; ++j) zero.v[j] = make_uint4(0u, 0u, 0u, 0u);
       const f32x4 z = contract16(vr.v, zero.v);
       bad = z[0] + z[1] + z[2] + z[3];
-      wave_lds_fence();
     } else {
 #pragma unroll
       for (int r = 0; r < 4; ++r) bad = not_finite<CPL>(va[r], bad);
@@ -418,13 +450,14 @@ __global__ void __launch_bounds__(256) na3d_any_fwd_kernel(const T* __restrict__
         return ldf(vb + (int64_t)run.tok[16 * ch + 4 * j + r] * D + e);
       });
     } else if constexpr (X) {
-      add_product16<CPL>(acc, tv[wave], m, g, pw);
+      add_product16<CPL>(acc, tv, m, g, pw);
     } else {
       add_product<CPL>(acc, va, pw);
     }
   });
   l = sum_over_rows(l);
   if (d.split > 1) {  // merge the waves of a tile: common reference, then sums
+    __syncthreads();  // every tile has been read
     if (part > 0) {
       float* buf = merge + (wave - wave / d.split - 1) * (64 * NS) + lane;
 #pragma unroll
@@ -539,10 +572,12 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
                                                           const float* __restrict__ lse, const float* __restrict__ dvec,
                                                           T* __restrict__ dq, AnyDims d) {
   using Fr = Frag<T, D>;
-  constexpr int CPL = D / 16, LD = D + 4;
-  __shared__ __attribute__((aligned(16))) float lds[4 * 16 * LD];
+  constexpr int CPL = D / 16, LD = D + 4, VT = X ? 4 * row16(D) : 16 * LD;  // floats of the V tile
+  constexpr int WAVE = 16 * LD + VT;
+  __shared__ __attribute__((aligned(16))) float lds[4 * WAVE];
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
   const Place at = wave_place(d, wave);
   const int part = at.part;
   const Walk w = Walk::make<false>(d, at.tile, m);
@@ -552,12 +587,12 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
   const float2* phq = ph ? ph + (int64_t)w.mine_in_plane() * (D / 2) : nullptr;
   const T *kb = k + base * D, *vb = v + base * D;
   const int64_t row = base + mine;
-  float* kt = lds + wave * 16 * LD;
+  float *kt = lds + wave * WAVE, *vt = kt + 16 * LD;
 
   float qf[Fr::N], gf[Fr::N];
   Fr::load(q + row * D, g, qf);
   if (phq) Fr::rotate(phq, g, qf);
-  if (d.norm) Fr::normalise(qf, d.eps);
+  if (d.norm) Fr::template normalise<false>(qf, d.eps);
   const float qs = d.scale * kLog2e;
 #pragma unroll
   for (int i = 0; i < Fr::N; ++i) qf[i] *= qs;
@@ -578,23 +613,28 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
 #pragma unroll
   for (int c = 0; c < CPL; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
-    const uint32_t p = run.pl[16 * ch + m], t = run.tok[16 * ch + m];
-    float kf[Fr::N];
-    Fr::load(kb + (int64_t)t * D, g, kf);
+    const uint32_t t = run.tok[16 * ch + lm];
+    float kf[Fr::N], vf[Fr::N];
+    typename Fr::Raw vr;
+    Fr::load(kb + (int64_t)t * D, lg, kf);
+    if constexpr (X) Fr::load(vb + (int64_t)t * D, lg, vr);
+    else Fr::load(vb + (int64_t)t * D, lg, vf);
+    if (ph) Fr::rotate(ph + (int64_t)run.pl[16 * ch + lm] * (D / 2), lg, kf);
+    if (d.norm) Fr::template normalise<true>(kf, d.eps);
+    wave_lds_fence();  // the last chunk's reads are done
+    Fr::to_lds(kt + lm * LD, lg, kf);
+    if constexpr (X) to_lds16(reinterpret_cast<char*>(vt), lm, lg, vr.v);
+    else Fr::to_lds(vt + lm * LD, lg, vf);
+    wave_lds_fence();
     f32x4 y;
     if constexpr (X) {
-      typename Fr::Raw vr;
-      Fr::load(vb + (int64_t)t * D, g, vr);
+      from_lds16(reinterpret_cast<const char*>(vt), m, g, vr.v);
       y = contract16(vr.v, gr.v);
     } else {
-      float vf[Fr::N];
-      Fr::load(vb + (int64_t)t * D, g, vf);
+      Fr::from_lds(vt + m * LD, g, vf);
       y = contract<Fr::N>(vf, gf);
     }
-    if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, kf);
-    if (d.norm) Fr::normalise(kf, d.eps);
-    wave_lds_fence();  // the last chunk's reads are done
-    Fr::to_lds(kt + m * LD, g, kf);
+    Fr::from_lds(kt + m * LD, g, kf);
     const f32x4 s = contract<Fr::N>(kf, qf);
     float ds[4];
 #pragma unroll
@@ -602,7 +642,6 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
       const float pw = __builtin_amdgcn_exp2f(fmaf(-L, kLog2e, s[r]));
       ds[r] = pick(see, r, pw * (y[r] - Dv), 0.f);
     }
-    wave_lds_fence();
     // a row of K~ that is not finite makes every score of its row so
     const float sv[4] = {s[0], s[1], s[2], s[3]};
     if (__any(not_finite<4>(sv, 0.f) != 0.f)) {
@@ -616,7 +655,7 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
   });
   if (d.split > 1) {
     __syncthreads();
-    merge_waves<CPL>(acc, lds, 16 * LD, wave, part, d.split, lane);
+    merge_waves<CPL>(acc, lds, WAVE, wave, part, d.split, lane);
   }
   if (at.store) finish_row<T, D>(acc, d.scale, q + row * D, phq, d, g, w.live, dq + row * D);
 }
@@ -634,6 +673,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 1) na3d_any_dkdv_kernel(con
   __shared__ __attribute__((aligned(16))) float lds[4 * WAVE];
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
   const Place at = wave_place(d, wave);
   const int part = at.part;
   const Walk w = Walk::make<true>(d, at.tile, m);
@@ -648,7 +688,7 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 1) na3d_any_dkdv_kernel(con
   float kf[Fr::N], vf[Fr::N];
   Fr::load(k + row * D, g, kf);
   if (phk) Fr::rotate(phk, g, kf);
-  if (d.norm) Fr::normalise(kf, d.eps);
+  if (d.norm) Fr::template normalise<false>(kf, d.eps);
   typename Fr::Raw vr;
   if constexpr (X) Fr::load(v + row * D, g, vr);
   else Fr::load(v + row * D, g, vf);
@@ -657,37 +697,40 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 1) na3d_any_dkdv_kernel(con
 #pragma unroll
   for (int c = 0; c < CPL; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   walk_box(w, run, d, part, lane, [&](uint32_t ch, uint32_t see) __attribute__((always_inline)) {
-    const uint32_t p = run.pl[16 * ch + m], t = run.tok[16 * ch + m];
+    const uint32_t t = run.tok[16 * ch + lm];
     float qf[Fr::N], gf[Fr::N];
-    Fr::load(qb + (int64_t)t * D, g, qf);
     typename Fr::Raw gr;
-    const float stat = g == 0 ? lse[base + t] : g == 1 ? dvec[base + t] : 0.f;
+    Fr::load(qb + (int64_t)t * D, lg, qf);
+    const float stat = lg == 0 ? lse[base + t] : lg == 1 ? dvec[base + t] : 0.f;
     if constexpr (X) {
-      Fr::load(gb + (int64_t)t * D, g, gr);
+      Fr::load(gb + (int64_t)t * D, lg, gr);
     } else {
-      Fr::load(gb + (int64_t)t * D, g, gf);
+      Fr::load(gb + (int64_t)t * D, lg, gf);
       if (lb) {
         float lf[Fr::N];
-        Fr::load(lb + (int64_t)t * D, g, lf);
+        Fr::load(lb + (int64_t)t * D, lg, lf);
 #pragma unroll
         for (int i = 0; i < Fr::N; ++i) gf[i] += lf[i];
       }
     }
-    if (ph) Fr::rotate(ph + (int64_t)p * (D / 2), g, qf);
-    if (d.norm) Fr::normalise(qf, d.eps);
+    if (ph) Fr::rotate(ph + (int64_t)run.pl[16 * ch + lm] * (D / 2), lg, qf);
+    if (d.norm) Fr::template normalise<true>(qf, d.eps);
     wave_lds_fence();  // the last chunk's reads are done
-    Fr::to_lds(qt + m * LD, g, qf);
+    Fr::to_lds(qt + lm * LD, lg, qf);
+    if constexpr (X) to_lds16(reinterpret_cast<char*>(gt), lm, lg, gr.v);
+    else Fr::to_lds(gt + lm * LD, lg, gf);
+    if (lg < 2) st[16 * lg + lm] = stat;
+    wave_lds_fence();
     f32x4 y;
     if constexpr (X) {
-      to_lds16(reinterpret_cast<char*>(gt), m, g, gr.v);
+      from_lds16(reinterpret_cast<const char*>(gt), m, g, gr.v);
       y = contract16(gr.v, vr.v);
     } else {
-      Fr::to_lds(gt + m * LD, g, gf);
+      Fr::from_lds(gt + m * LD, g, gf);
       y = contract<Fr::N>(gf, vf);
     }
-    if (g < 2) st[lane] = stat;
+    Fr::from_lds(qt + m * LD, g, qf);
     const f32x4 s = contract<Fr::N>(qf, kf);
-    wave_lds_fence();
     const float4 L = *reinterpret_cast<const float4*>(st + 4 * g), Dv = *reinterpret_cast<const float4*>(st + 16 + 4 * g);
     const float Ls[4] = {L.x, L.y, L.z, L.w}, Ds[4] = {Dv.x, Dv.y, Dv.z, Dv.w};
     float pw[4], ds[4];
