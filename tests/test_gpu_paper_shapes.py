@@ -315,6 +315,27 @@ def test_d128_w999_bwd_sampled_keys(shape, rope):
     check_close(host_rows(dv, sel, d), refs[2], "bf16", "dv")
 
 
+@pytest.mark.parametrize("qk_norm,gkind", [(False, 0), (True, "d")])
+@pytest.mark.parametrize("shape", [(1, 2, 9, 9, 9, 128),     # one window of query rows a level
+                                   (1, 1, 10, 10, 19, 128),  # an odd number of levels, two and three windows
+                                   (2, 1, 17, 12, 14, 128)])  # key levels past the last block's first
+def test_d128_w999_bwd_query_windows(shape, qk_norm, gkind):
+    """The query box staged in one, two or three windows per level, in turn in two
+    buffers, with and without the low term of the gated gradient: dq of every query,
+    dk and dv of sampled keys against the oracle."""
+    window = (9, 9, 9)
+    r = run(shape, window, "bf16", 90, qk_norm=qk_norm, gkind=gkind, bwd=True)
+    q, k, v, g = r["inputs"]
+    sel = sample_keys(shape, 96, 91)
+    w = lambda a: None if a is None else oracle.widen(a, "bf16")
+    refs = oracle.na3d_bwd(w(q), w(k), w(v), w(r["dout"]), window, r["scale"], coords=r["c32"], selk=sel,
+                           qk_norm=qk_norm, gate=w(g))
+    d = shape[-1]
+    check_close(host_f64(r["grads"][0]), refs[0], "bf16", "dq")
+    check_close(host_rows(r["grads"][1], sel, d), refs[1], "bf16", "dk")
+    check_close(host_rows(r["grads"][2], sel, d), refs[2], "bf16", "dv")
+
+
 def test_d128_w999_bwd_decoder_full_size_sampled():
     """The decoder shape's backward in one launch each; sampled queries and keys
     against the oracle on both tiles."""
