@@ -108,6 +108,14 @@ __device__ __forceinline__ void st16(char* p, uint4 v) {
   *reinterpret_cast<u32x4*>(p) = u32x4{v.x, v.y, v.z, v.w};
 }
 
+// Column swizzle of 256-byte rows (16 columns of 16 bytes, XORed with it): row u
+// of the walk takes a value of its own among 16 consecutive rows, so that a
+// 16-byte read of 16 rows at one column reaches every bank once, and its upper
+// three bits differ among 8 rows, so that a transpose read of 8 rows x 32 bytes
+// does too.  (256 bytes are all 64 banks: a swizzle that leaves out the row's
+// lowest bit, as 128-byte rows take it, sends every two rows to the same banks.)
+__device__ __forceinline__ int swizzle16(int u) { return ((u & 7) << 1) | ((u >> 3) & 1); }
+
 // Direct global -> LDS copy of 16 bytes per lane: lane i of the wave writes
 // wave_dst + 16 i (wave_dst must be the same for the whole wave).
 __device__ __forceinline__ void copy16_to_lds(const uint16_t* src, char* wave_dst) {

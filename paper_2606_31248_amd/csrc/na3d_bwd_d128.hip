@@ -38,7 +38,8 @@
 // 256 bytes each with swizzled columns, are staged with LSE and -D in windows of
 // 96 rows, double buffered: the next window's copies run under the current one's
 // products, and the phases of a slot, the same on every level, stay in registers
-// (decoder shape, forward + backward: 1565 -> 1517 us).  Per (key level, query level) a wave walks the box
+// (decoder shape, forward + backward: 1565 -> 1517 us; with a column swizzle of
+// four bits in the three head_dim-128 kernels 1386 us).  Per (key level, query level) a wave walks the box
 // in steps of 32 queries:
 //   X = Q~ . K~^T seeded with -LSE (or -inf outside the window), P = exp2(X);
 //   Y = dO . V^T - D;
@@ -133,7 +134,7 @@ __global__ void __launch_bounds__(256 * NG, 1) na3d_bwd_dq_d128_kernel(Args a) {
   const int qy = min(qy_raw, H - 1), qx = min(qx_raw, W - 1);
   const int wys = win_start(qy, H, KY), wxs = win_start(qx, W, KX);
 
-  auto kswz = [&](int key) { return ((key % C::LX >> 1) + 5 * (key / C::LX)) & 7; };
+  auto kswz = [&](int key) { return swizzle16(key % C::LX + C::NUX * (key / C::LX)); };
   auto key_row = [&](int u) {
     return u < C::NU ? (uy0 - ty0 + u / C::NUX) * C::LX + (ux0 - tx0 + u % C::NUX) : 0;
   };
@@ -398,7 +399,6 @@ constexpr int kRow = 256;  // staged query row (Q~ float16 or dO bf16)
 // queries whose (border-clamped) window holds position j of an axis of extent L
 __host__ __device__ __forceinline__ int inv_lo(int j, int k) { return j < k ? 0 : j - (k >> 1); }
 __host__ __device__ __forceinline__ int inv_hi(int j, int L, int k) { return j >= L - k ? L - 1 : j + (k >> 1); }
-__device__ __forceinline__ int rswz(int u) { return (((u >> 1) & 3) << 1) | ((u >> 3) & 1); }
 
 // The query box is staged in row windows of RW rows, double buffered: the 144
 // rows of a box away from the borders (160 with the last step's padding) take
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(64 * ZK, 1) na3d_bwd_dkdv_d128_kernel(Args a) 
   for (int w = 0; w < C::NW; ++w)
 #pragma unroll
     for (int it = 0; it < C::IT; ++it) {
-      const int s = it * kThreads + tid, r = s >> 4, u = w * C::RW + r, dc = (s & 15) ^ rswz(r);
+      const int s = it * kThreads + tid, r = s >> 4, u = w * C::RW + r, dc = (s & 15) ^ swizzle16(r);
       const int uc = min(u, nq - 1);
       goff[w][it] = u < npairs * 32 ? ((qy0 + uc / nqx) * W + qx0 + uc % nqx) * kD + dc * 8 : -1;
       ph[w][it] = make_uint4(0u, 0u, 0u, 0u);
@@ -593,11 +593,11 @@ __global__ void __launch_bounds__(64 * ZK, 1) na3d_bwd_dkdv_d128_kernel(Args a) 
   int ex = kMinExp;
 
   // A rows: chunk c, row 16c + qn, column g (k-step kk: xor 64 kk bytes)
-  const uint32_t aoff = qn * kRow + ((g ^ rswz(qn)) << 4);
+  const uint32_t aoff = qn * kRow + ((g ^ swizzle16(qn)) << 4);
   // transpose reads: row 32 st + 4g + qn/4 (+16 for the second chunk), the 8
   // bytes holding elements 4 (qn % 4) .. +3 of each 16-wide d block (xor 32 t)
   const int trow = 4 * g + (qn >> 2);
-  const uint32_t toff = trow * kRow + ((((qn >> 1) & 1) ^ rswz(trow)) << 4) + 8 * (qn & 1);
+  const uint32_t toff = trow * kRow + ((((qn >> 1) & 1) ^ swizzle16(trow)) << 4) + 8 * (qn & 1);
 
   auto compute = [&](int p, int w, const char* tQ, const char* tG, const char* tL) __attribute__((always_inline)) {
     const float* sLp = sL[p & 1];

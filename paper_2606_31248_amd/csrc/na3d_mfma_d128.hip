@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(kThreads, 1) na3d_fwd_d128_kernel(Args a) {
   const int qy = min(qy_raw, H - 1), qx = min(qx_raw, W - 1);
   const int wys = win_start(qy, H, KY), wxs = win_start(qx, W, KX);
 
-  auto kswz = [&](int key) { return ((key % C::LX >> 1) + 5 * (key / C::LX)) & 7; };
+  auto kswz = [&](int key) { return swizzle16(key % C::LX + C::NUX * (key / C::LX)); };
   auto key_row = [&](int u) {
     return u < C::NU ? (uy0 - ty0 + u / C::NUX) * C::LX + (ux0 - tx0 + u % C::NUX) : 0;
   };
