@@ -434,13 +434,21 @@ __global__ void __launch_bounds__(64 * ZK, 1) na3d_bwd_dkdv_d128_kernel(Args a) 
   __shared__ __attribute__((aligned(16))) float sD[2][C::MQ];
   __shared__ __attribute__((aligned(16))) unsigned short smask[C::MQ];
 
-  const int nblk = gridDim.x;
-  int bid = blockIdx.x;
-  if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);
-  const int xb = bid % a.n_xb;
-  const int yb = (bid / a.n_xb) % a.n_yb;
-  const int zb = (bid / (a.n_xb * a.n_yb)) % a.n_zb;
-  const int bh = bid / (a.n_xb * a.n_yb * a.n_zb);
+  // An XCD takes neighbouring places of the (head, y, x) grid, at every level
+  // group: keys in the middle of the column are seen by up to twice the query
+  // levels of those near its ends (24 of 24 levels against 12), so an XCD with the
+  // middle groups only would end last.  The middle group goes first: its longer
+  // workgroups start when all CUs are free.  Decoder shape: 895 us with the level
+  // group outermost over the whole grid, 708 us now.
+  const int places = gridDim.x / a.n_zb;
+  const int per = (places & 7) == 0 ? places >> 3 : places;
+  const int xcd = (places & 7) == 0 ? blockIdx.x & 7 : 0;
+  const int bid = (places & 7) == 0 ? blockIdx.x >> 3 : blockIdx.x;
+  const int zi = bid / per, place = xcd * per + bid % per;
+  const int zb = zi & 1 ? a.n_zb / 2 - (zi + 1) / 2 : a.n_zb / 2 + zi / 2;
+  const int xb = place % a.n_xb;
+  const int yb = (place / a.n_xb) % a.n_yb;
+  const int bh = place / (a.n_xb * a.n_yb);
   const int b = bh / a.heads;
   const int H = a.H, W = a.W, Z = a.Z;
   const int y0 = 4 * yb, x0 = 4 * xb, z0 = ZK * zb;
