@@ -231,8 +231,10 @@ strata_status strata_na3d_fwd_ex(const strata_na3d_desc* desc, const strata_na3d
  * dgate: same shape and dtype as the gate, required when opts->gate is set
  * (NULL otherwise).  workspace: at least strata_na3d_bwd_ex_workspace_size(desc,
  * opts) bytes of device memory owned by the caller; it holds D and, with a
- * gate, dA (for bf16 as two bf16 terms whose sum carries it to ~2^-16).  The
- * norm is applied inside the attention kernels.  The library allocates
+ * gate, dA (for bf16 with a logit per channel as two bf16 terms whose sum
+ * carries it to ~2^-16; with one logit per token-head 2^e dO, which is exact,
+ * and lse - ln f, where sigmoid(g) = f 2^e).  The norm is applied inside the
+ * attention kernels.  The library allocates
  * nothing. */
 size_t strata_na3d_bwd_ex_workspace_size(const strata_na3d_desc* desc,
                                          const strata_na3d_opts* opts);
