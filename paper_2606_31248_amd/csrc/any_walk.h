@@ -30,6 +30,7 @@ struct AnyDims {
   FastDiv ty, tx;         // tiles along y and x
   FastDiv places;         // tiles of one grid
   uint32_t nbh;           // grids: batch * heads
+  uint32_t blocks;        // workgroups
   int split;              // waves of a workgroup that share a tile's chunks (1, 2 or 4); the others take the
                           // same tile of the next 4 / split grids
   float scale;
@@ -159,6 +160,12 @@ __host__ __device__ __forceinline__ void fill_run(const Walk& w, Run& t, uint32_
 // Tokens that a block of b positions of an axis reaches, at most
 inline int box_extent(int b, int L, int k) { return L < b + k - 1 ? L : b + k - 1; }
 
+// workgroups of a problem: every tile of a grid for one group of grids, then the next group
+inline int64_t any_blocks(const AnyDims& d) {
+  const int64_t per = 4 / d.split;
+  return ((int64_t)d.nbh + per - 1) / per * d.places.n;
+}
+
 // The tile's shape: of the 15 ways to write 16 = bz by bx, the one that needs
 // the fewest chunks over the whole grid (ragged edges included), the longest in
 // x among equals (its loads are the most contiguous).  A plane window takes
@@ -187,18 +194,34 @@ inline AnyDims any_dims(int B, int heads, int Z, int H, int W, int kz, int ky, i
   int split = tiles * nbh >= 4096 ? 1 : tiles * nbh >= 2048 ? 2 : 4;
   auto idle = [nbh](int per) { return (nbh + per - 1) / per * per * 20 > nbh * 23; };
   while (split < 4 && idle(4 / split)) split *= 2;
-  return AnyDims{heads, Z, H, W, kz, ky, kx, best[0], best[1], best[2], count(H, best[1]), count(W, best[2]),
-                 FastDiv((uint32_t)tiles), (uint32_t)nbh, split, scale, norm, eps};
+  AnyDims d{heads, Z, H, W, kz, ky, kx, best[0], best[1], best[2], count(H, best[1]), count(W, best[2]),
+            FastDiv((uint32_t)tiles), (uint32_t)nbh, 0, split, scale, norm, eps};
+  d.blocks = (uint32_t)any_blocks(d);
+  return d;
 }
 
-// workgroups of a problem: every tile of a grid for one group of grids, then the next group
-inline int64_t any_blocks(const AnyDims& d) {
-  const int64_t per = 4 / d.split;
-  return ((int64_t)d.nbh + per - 1) / per * d.places.n;
+// The launch grid of n workgroups.  A dimension of it holds fewer than 2^32
+// threads, so of 256-thread workgroups at most 2^24 - 1: more than 2^23 go into
+// rows of 2^23, and those of the last row past the n-th do nothing.
+struct LaunchGrid {
+  uint32_t x, y;
+};
+inline LaunchGrid launch_grid(int64_t n) {
+  const int64_t row = (int64_t)1 << 23;
+  return n <= row ? LaunchGrid{(uint32_t)n, 1} : LaunchGrid{(uint32_t)row, (uint32_t)((n + row - 1) / row)};
+}
+
+// The place in the problem of the i-th workgroup launched, of n.  Consecutive
+// places stay on one XCD (workgroups are handed to the eight XCDs in turn): they
+// share most of their box.
+__host__ __device__ __forceinline__ uint32_t xcd_order(uint32_t i, uint32_t n) {
+  const uint32_t q = n / 8, r = n % 8, x = i % 8;
+  return x * q + min(x, r) + i / 8;
 }
 
 // Whether the 32-bit token and block indices above hold: every problem that a
-// device can hold (2^32 tokens of the narrowest rows are 256 GiB a tensor).
+// device can hold (2^32 tokens of the narrowest rows are 256 GiB a tensor) and
+// whose windows can be walked in a lifetime.
 inline bool any_fits(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
   // a box spans at most 16 + 1.5 k positions of an axis (the queries that see keys near a border)
   auto most = [](int L, int k) { return (double)(L < 16 + k + k / 2 ? L : 16 + k + k / 2); };

@@ -313,12 +313,6 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Consecutive tiles stay on one XCD (blocks are handed to the eight XCDs in turn): they share most of their box.
-__device__ __forceinline__ uint32_t xcd_block() {
-  const uint32_t n = gridDim.x, q = n / 8, r = n % 8, x = blockIdx.x % 8;
-  return x * q + min(x, r) + blockIdx.x / 8;
-}
-
 // The workgroup's tile (a place in the grid), and the wave's grid (batch * heads +
 // head) and part of the chunks; waves past the last grid repeat it and store nothing.
 struct Place {
@@ -327,8 +321,8 @@ struct Place {
   int b, part;
   bool store;
 };
-__device__ __forceinline__ Place wave_place(const AnyDims& d, int wave) {
-  const uint32_t blk = xcd_block(), grp = d.places.div(blk), bh = grp * (4 / d.split) + wave / d.split;
+__device__ __forceinline__ Place wave_place(const AnyDims& d, uint32_t launched, int wave) {
+  const uint32_t blk = xcd_order(launched, d.blocks), grp = d.places.div(blk), bh = grp * (4 / d.split) + wave / d.split;
   const uint32_t in = min(bh, d.nbh - 1);
   const int part = wave % d.split;
   return Place{blk - grp * d.places.n, (int64_t)in, (int)(in / (uint32_t)d.heads), part, bh < d.nbh && part == 0};
@@ -372,7 +366,9 @@ __global__ void __launch_bounds__(256, D == 64 && sizeof(T) == 2 ? 4 : 1) na3d_a
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
-  const Place at = wave_place(d, wave);
+  const uint32_t launched = blockIdx.y * gridDim.x + blockIdx.x;
+  if (launched >= d.blocks) return;
+  const Place at = wave_place(d, launched, wave);
   const int part = at.part;
   const Walk w = Walk::make<false>(d, at.tile, m);
   const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
@@ -578,7 +574,9 @@ __global__ void __launch_bounds__(256, D == 64 ? (X ? 4 : 3) : 1) na3d_any_dq_ke
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
-  const Place at = wave_place(d, wave);
+  const uint32_t launched = blockIdx.y * gridDim.x + blockIdx.x;
+  if (launched >= d.blocks) return;
+  const Place at = wave_place(d, launched, wave);
   const int part = at.part;
   const Walk w = Walk::make<false>(d, at.tile, m);
   const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
@@ -674,7 +672,9 @@ __global__ void __launch_bounds__(256, D == 64 ? 3 : 1) na3d_any_dkdv_kernel(con
   __shared__ __attribute__((aligned(16))) Run run;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   const int lm = lane >> 2, lg = lane & 3;  // row and piece that the lane loads
-  const Place at = wave_place(d, wave);
+  const uint32_t launched = blockIdx.y * gridDim.x + blockIdx.x;
+  if (launched >= d.blocks) return;
+  const Place at = wave_place(d, launched, wave);
   const int part = at.part;
   const Walk w = Walk::make<true>(d, at.tile, m);
   const int64_t n_tok = (int64_t)d.Z * d.H * d.W, base = at.bh * n_tok;
@@ -806,7 +806,10 @@ __global__ void __launch_bounds__(256) na3d_bwd_pre_kernel(const T* __restrict__
   if (row < nq && c == 0) dvec[row] = acc;
 }
 
-dim3 any_grid(const AnyDims& a) { return dim3((uint32_t)any_blocks(a)); }
+dim3 any_grid(const AnyDims& a) {
+  const LaunchGrid g = launch_grid(a.blocks);
+  return dim3(g.x, g.y);
+}
 
 template <typename T, int D>
 void fwd_any(const strata_na3d_desc& d, const NaOpts& o, const void* q, const void* k, const void* v, const float* cs,

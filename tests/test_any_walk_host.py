@@ -42,7 +42,7 @@ template <bool INV>
 static int check(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
   const AnyDims d = any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f);
   const int N = Z * H * W, per = 4 / d.split;
-  if (d.nbh != (uint32_t)(B * heads) || any_blocks(d) != (int64_t)d.places.n * ((B * heads + per - 1) / per)) return printf("blocks\n"), 1;
+  if (d.nbh != (uint32_t)(B * heads) || (int64_t)d.blocks != any_blocks(d) || any_blocks(d) != (int64_t)d.places.n * ((B * heads + per - 1) / per)) return printf("blocks\n"), 1;
   std::vector<int> cover(N, 0);
   static Run run;
   for (uint32_t t = 0; t < d.places.n; ++t) {
@@ -111,6 +111,24 @@ int main() {
     const int per = 4 / d.split, groups = (bh + per - 1) / per;
     if (groups * per < bh || groups * per > bh * 1.15 + 1e-9) return printf("%d grids: %d x %d\n", bh, groups, per), 1;
   }
+  // launch grids: under 2^32 threads a dimension, every workgroup of the problem launched, and by any number
+  // of launched ones every place taken once
+  for (int64_t n : {(int64_t)1, (int64_t)8191, ((int64_t)1 << 24) - 1, (int64_t)1 << 24, ((int64_t)1 << 24) + 4, ((int64_t)1 << 30) - 1}) {
+    const LaunchGrid g = launch_grid(n);
+    if ((uint64_t)g.x * 256 >= 1ull << 32 || g.y > 65535 || (int64_t)g.x * g.y < n || (g.y > 1 && g.x % 8)) return printf("launch of %lld\n", (long long)n), 1;
+    if (g.y == 1 && (int64_t)g.x != n) return printf("idle workgroups\n"), 1;
+  }
+  for (uint32_t n = 1; n < 600; ++n) {
+    std::vector<int> seen(n, 0);
+    for (uint32_t i = 0; i < n; ++i) {
+      const uint32_t at = xcd_order(i, n);
+      if (at >= n || seen[at]++) return printf("order of %u\n", n), 1;
+    }
+  }
+  // 24 x 3345 x 3345 tokens of one (batch, head), 2^26 grids of one token: both hold, both need more than 2^24 workgroups
+  for (const AnyDims& d : {any_dims(1, 1, 24, 3345, 3345, 3, 3, 3, 1.f, 0, 0.f), any_dims(1 << 22, 17, 1, 1, 1, 1, 1, 1, 1.f, 0, 0.f)})
+    if (d.blocks < 1u << 24 || (int64_t)d.blocks != any_blocks(d) || (uint64_t)launch_grid(d.blocks).x * 256 >= 1ull << 32) return printf("large\n"), 1;
+  if (!any_fits(1, 1, 24, 3345, 3345, 3, 3, 3) || !any_fits(1 << 22, 17, 1, 1, 1, 1, 1, 1)) return printf("large fits\n"), 1;
   if (any_fits(1, 1, 1 << 12, 1 << 12, 1 << 12, 3, 3, 3) || !any_fits(81, 16, 24, 128, 128, 9, 9, 9) || !any_fits(1 << 13, 1 << 13, 1, 1, 1, 1, 1, 1)) return printf("fits\n"), 1;
   printf("ok\n");
   return 0;

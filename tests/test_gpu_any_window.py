@@ -83,3 +83,24 @@ def test_values_that_are_not_finite_stay_in_their_windows(dtype, d, bad):
         assert 0 < np.count_nonzero(~fine) < ref.size // 2
         assert np.array_equal(np.isfinite(got), fine), name
         check_close(got[fine], ref[fine], dtype, name)
+
+
+def test_more_workgroups_than_one_grid_dimension_holds():
+    """2^26 + 2^22 grids of one token: 17.8 million workgroups of 256 threads.  Every token sees itself alone: out = v,
+    lse = scale <q, k>, dv = dO."""
+    shape, base = (1 << 22, 17, 1, 1, 1, 32), 1 << 12
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v, g = (torch.randn((base,) + shape[1:], generator=gen, device="cuda").to(torch.bfloat16).repeat((shape[0] // base,) + (1,) * 5)
+                  for _ in range(4))
+    desc = B.desc_for(q, (1, 1, 1), 0.25)
+    out, lse = torch.empty_like(q), torch.empty(shape[:-1], dtype=torch.float32, device="cuda")
+    B.strata_na3d_fwd(desc, q, k, v, None, out, lse)
+    assert torch.equal(out, v)
+    want = 0.25 * (q[:base].double() * k[:base].double()).sum(-1)
+    assert (lse.view(-1, *want.shape).double() - want).abs().max() <= 1e-5
+    ws = torch.empty(B.strata_na3d_bwd_workspace_size(desc), dtype=torch.uint8, device="cuda")
+    dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
+    B.strata_na3d_bwd(desc, q, k, v, None, out, g, lse, dq, dk, dv, ws)
+    assert torch.equal(dv, g)
+    for t in (dq, dk):  # rounding of D against <dO, v>
+        assert t.abs().max() <= 1e-4
