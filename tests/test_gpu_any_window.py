@@ -13,7 +13,7 @@ import torch
 import oracle
 from paper_2606_31248_amd import binding as B
 from paper_2606_31248_amd import inputs as I
-from _util import F32_ABS, bf16_half_ulp, check_close, host_f64
+from _util import F32_ABS, bf16_half_ulp, check_close, dev_tensor, host_f64
 from test_gpu_parity import gpu_phases, oracle_coords, run_bwd, run_fwd
 
 pytestmark = pytest.mark.gpu
@@ -83,6 +83,41 @@ def test_values_that_are_not_finite_stay_in_their_windows(dtype, d, bad):
         assert 0 < np.count_nonzero(~fine) < ref.size // 2
         assert np.array_equal(np.isfinite(got), fine), name
         check_close(got[fine], ref[fine], dtype, name)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_token_that_sees_itself_alone(dtype):
+    """One score per query and a scale that is a power of two: the score less its lse is 0, the weight 1 and no sum is
+    rounded, so out = v and dv = dO bit for bit."""
+    shape = (1, 3, 3, 6, 17, 32)
+    q, k, v, g = (I.gaussian(shape, 53, s, dtype) for s in (0, 1, 2, I.STREAM_DO))
+    qd, kd, vd, gd = (dev_tensor(a, dtype) for a in (q, k, v, g))
+    desc, cs = B.desc_for(qd, (1, 1, 1), 0.125), gpu_phases(oracle_coords(I.random_placement(1, 6, 17, 97), 6, 17), 32)
+    out, lse = torch.empty_like(qd), torch.empty(shape[:-1], dtype=torch.float32, device="cuda")
+    B.strata_na3d_fwd(desc, qd, kd, vd, cs, out, lse)
+    ws = torch.empty(B.strata_na3d_bwd_workspace_size(desc), dtype=torch.uint8, device="cuda")
+    dq, dk, dv = (torch.empty_like(qd) for _ in range(3))
+    B.strata_na3d_bwd(desc, qd, kd, vd, cs, out, gd, lse, dq, dk, dv, ws)
+    assert torch.equal(out, vd) and torch.equal(dv, gd)
+
+
+# relative error (2-norm) of float32 results where every query's scores are summed, exponentiated with expf and
+# accumulated by one thread or wave per query, on inputs of the same distribution
+@pytest.mark.parametrize("d,window,most", [
+    (64, (3, 3, 3), dict(out=2.2e-7, dq=3.1e-7, dk=3.1e-7, dv=2.8e-7)),
+    (32, (3, 7, 7), dict(out=2.2e-7, dq=4.1e-7, dk=4.2e-7, dv=4.1e-7)),
+    (64, (5, 9, 9), dict(out=3.0e-7, dq=5.7e-7, dk=6.0e-7, dv=5.8e-7)),
+])
+def test_float32_error(d, window, most):
+    shape = (1, 2, 6, 14, 17, d)
+    c32 = oracle_coords(I.random_placement(1, 14, 17, 97), 14, 17)
+    (q, k, v), out, _, scale = run_fwd(shape, window, "f32", 54, c32)
+    (q, k, v, g), grads, scale = run_bwd(shape, window, "f32", 54, c32)
+    wide = [oracle.widen(a, "f32") for a in (q, k, v, g)]
+    refs = (oracle.na3d_fwd(*wide[:3], window, scale, coords=c32)[0],) + tuple(oracle.na3d_bwd(*wide, window, scale, coords=c32))
+    for (name, bound), got, ref in zip(most.items(), [out] + list(grads), refs):
+        err = np.linalg.norm(host_f64(got) - ref) / np.linalg.norm(ref)
+        assert err <= bound, f"{name}: {err:.2e}"
 
 
 def test_more_workgroups_than_one_grid_dimension_holds():
