@@ -204,12 +204,14 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   // D = rowsum(dO * O): from the gate's pass, from the MFMA dq pass (which reads
   // O beside the dO rows it loads anyway), or from a pass of its own
   const bool fuse_d = !o.gate && na3d_bwd_dq_mfma_takes(*desc);
+  bool one_block = false;  // no balanced dk/dv pass
   if (o.gate && o.gate_dim == 1 && desc->dtype == STRATA_BF16) {
     // lse' where the low term of a two-term dA would be (4 bytes of its row)
     float* lse_f = reinterpret_cast<float*>(ws + L.da_lo);
     launch_na3d_bwd_gate_row_prep(*desc, o, out, dout, lse, lse_f, dvec, ws + L.da_hi, dgate, s);
     ga = ws + L.da_hi;
     lse = lse_f;
+    one_block = !na3d_bwd_dkdv_kvp_fills(*desc);
   } else if (o.gate) {
     void* lo = desc->dtype == STRATA_BF16 ? ws + L.da_lo : nullptr;
     launch_na3d_bwd_gate_prep(*desc, o, out, dout, dvec, ws + L.da_hi, lo, dgate, s);
@@ -221,7 +223,7 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   // the MFMA dq pass also records the largest |dO| exponent per (batch, head)
   // when the balanced dk/dv pass, which scales its float16 copy of dO by it,
   // takes the problem
-  int* emax = na3d_bwd_dkdv_kvp_takes(*desc, bo) ? reinterpret_cast<int*>(ws + L.emax) : nullptr;
+  int* emax = !one_block && na3d_bwd_dkdv_kvp_takes(*desc, bo) ? reinterpret_cast<int*>(ws + L.emax) : nullptr;
   if (!launch_na3d_bwd_dq_mfma(*desc, bo, q, k, v, cs, ga, lse, dvec, fuse_d ? out : nullptr, emax, dq, s)) {
     emax = nullptr;
     if (fuse_d) launch_na3d_bwd_any(0, *desc, bo, q, k, v, cs, out, dout, lse, dq, dk, dv, dvec, s);

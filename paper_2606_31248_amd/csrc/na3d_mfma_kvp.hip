@@ -651,6 +651,10 @@ bool na3d_bwd_dkdv_kvp_takes(const strata_na3d_desc& d, const BwdOpts& o) {
   return (int64_t)d.B * d.heads * n_groups(d.H) * n_groups(d.W) < (int64_t)1 << 31;
 }
 
+bool na3d_bwd_dkdv_kvp_fills(const strata_na3d_desc& d) {
+  return fills_chip((int64_t)d.B * d.heads * n_groups(d.H) * n_groups(d.W));
+}
+
 bool launch_na3d_bwd_dkdv_kvp(const strata_na3d_desc& d, const BwdOpts& o, const void* q, const void* k,
                               const void* v, const float* cs, const void* dout, const float* lse,
                               const float* dvec, const int* emax, void* dk, void* dv, hipStream_t s) {

@@ -18,7 +18,7 @@ LOGITS = np.array([-200.0, -60.0, -20.0, -3.0, 0.0, 4.0, 30.0], np.float32)
 
 
 @pytest.mark.parametrize("shape,window", [
-    ((1, 2, 5, 13, 12, 64), (5, 9, 9)),     # balanced dK/dV
+    ((1, 2, 5, 13, 12, 64), (5, 9, 9)),     # one-block dK/dV, 9-wide
     ((1, 2, 5, 13, 11, 64), (3, 7, 7)),     # one-block dK/dV
     ((2, 2, 20, 3, 5, 64), (20, 1, 1)),     # columns of two blocks
     ((1, 2, 9, 4, 5, 64), (5, 1, 1)),       # columns of one block

@@ -83,6 +83,12 @@ int main() {
       }
     }
   }
+  for (int n = 1; n <= 5000; ++n) {  // one workgroup to a CU, rounds of 256: 7/8 of the last round's CUs and all others
+    int rounds = 0, left = n;
+    while (left > 0) { left -= 256; ++rounds; }
+    if (fills_chip(n) != (8 * n >= 7 * 256 * rounds)) { printf("%d workgroups\n", n); return 1; }
+  }
+  if (fills_chip(16) || fills_chip(223) || !fills_chip(224) || !fills_chip(256) || fills_chip(257) || !fills_chip(1536)) return 1;
   printf("ok %ld\n", checks);
   return 0;
 }
