@@ -161,11 +161,12 @@ strata_status strata_na3d_fwd(const strata_na3d_desc* desc, const void* q, const
  * Kernels and input range as strata_na3d_fwd; on the MFMA paths the dS products
  * (dq, dk) are float16 with exact power-of-two scaling; P.dO and dO.V^T are
  * float16 products with dO scaled by a power of two per (batch, head) in the
- * dK/dV kernel of the 9-wide windows (V then saturates at 65504 and keeps
- * float16's subnormal spacing below 2^-14, as in the level-sweep forward);
- * elsewhere they are bf16 products, P.dO with P in two bf16 terms in the
- * one-block dK/dV kernel (3x7x7, planes of 17-20 positions; one term with the
- * gate's two-term dA) and with P rounded to bf16 once in the column and
+ * balanced dK/dV kernel of the 9-wide windows (V then saturates at 65504 and
+ * keeps float16's subnormal spacing below 2^-14, as in the level-sweep forward;
+ * with a gate it takes only (batch, head)s inside these ranges, see
+ * strata_na3d_bwd_ex); elsewhere they are bf16 products, P.dO with P in two bf16
+ * terms in the one-block dK/dV kernel (3x7x7, and the 9-wide windows with a gate;
+ * one term with a two-term dA) and with P rounded to bf16 once in the column and
  * head_dim-128 kernels. */
 size_t strata_na3d_bwd_workspace_size(const strata_na3d_desc* desc);
 strata_status strata_na3d_bwd(const strata_na3d_desc* desc, const void* q, const void* k,
@@ -233,8 +234,12 @@ strata_status strata_na3d_fwd_ex(const strata_na3d_desc* desc, const strata_na3d
  * opts) bytes of device memory owned by the caller; it holds D and, with a
  * gate, dA (for bf16 with a logit per channel as two bf16 terms whose sum
  * carries it to ~2^-16; with one logit per token-head 2^e dO, which is exact,
- * and lse - ln f, where sigmoid(g) = f 2^e).  The norm is applied inside the
- * attention kernels.  The library allocates
+ * and lse - ln f, where sigmoid(g) = f 2^e).  With a gate every product of dO and
+ * V keeps bf16's range: with one logit per token-head at 5x9x9 and 9x9x9 a (batch,
+ * head) takes the balanced dK/dV kernel only where 2^e dO spans less than 2^24 from
+ * row to row and V's rows lie between 2^-10 and 2^16 (their largest magnitudes),
+ * and the one-block kernel otherwise, as does a problem too small to fill the chip.
+ * The norm is applied inside the attention kernels.  The library allocates
  * nothing. */
 size_t strata_na3d_bwd_ex_workspace_size(const strata_na3d_desc* desc,
                                          const strata_na3d_opts* opts);

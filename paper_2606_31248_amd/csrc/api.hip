@@ -87,8 +87,11 @@ static strata_status check_opts(const strata_na3d_desc* d, const strata_na3d_opt
 }
 
 // Backward workspace: D, the per-(batch, head) exponent of the largest |dO|,
-// then (with a gate) dA = sigmoid(g) dO as its rounded value hi and, for bf16,
-// the remainder lo; every region starts on a 256-byte boundary.
+// then with a gate dA = sigmoid(g) dO, which is for bf16 its rounded value hi and
+// the remainder lo.  With one bf16 logit per token-head hi holds 2^e dO instead and
+// lo's place (at least 64 bytes a row) lse' = lse - ln f and, where the balanced
+// dk/dv pass may run, a word per row and one per (batch, head).  Every region starts
+// on a 256-byte boundary.
 struct BwdLayout {
   size_t dvec, emax, da_hi, da_lo, total;
 };
@@ -206,12 +209,18 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
   const bool fuse_d = !o.gate && na3d_bwd_dq_mfma_takes(*desc);
   bool one_block = false;  // no balanced dk/dv pass
   if (o.gate && o.gate_dim == 1 && desc->dtype == STRATA_BF16) {
-    // lse' where the low term of a two-term dA would be (4 bytes of its row)
     float* lse_f = reinterpret_cast<float*>(ws + L.da_lo);
-    launch_na3d_bwd_gate_row_prep(*desc, o, out, dout, lse, lse_f, dvec, ws + L.da_hi, dgate, s);
+    const size_t n = (size_t)desc->B * desc->heads * desc->Z * desc->H * desc->W;
+    // the balanced dk/dv pass takes the (batch, head)s inside its float16 ranges, if it fills the chip
+    const bool balanced = na3d_bwd_dkdv_kvp_takes(*desc, bo) && na3d_bwd_dkdv_kvp_fills(*desc);
+    uint32_t* row_max = reinterpret_cast<uint32_t*>(lse_f + n);
+    int* fits = reinterpret_cast<int*>(row_max + n);
+    launch_na3d_bwd_gate_row_prep(*desc, o, out, dout, lse, balanced ? v : nullptr, lse_f, dvec, ws + L.da_hi, dgate,
+                                  row_max, fits, s);
     ga = ws + L.da_hi;
     lse = lse_f;
-    one_block = !na3d_bwd_dkdv_kvp_fills(*desc);
+    one_block = !balanced;
+    bo.fits = balanced ? fits : nullptr;
   } else if (o.gate) {
     void* lo = desc->dtype == STRATA_BF16 ? ws + L.da_lo : nullptr;
     launch_na3d_bwd_gate_prep(*desc, o, out, dout, dvec, ws + L.da_hi, lo, dgate, s);
@@ -230,7 +239,9 @@ static strata_status na3d_bwd_launch(const strata_na3d_desc* desc, const strata_
     if (!launch_na3d_bwd_dq_d128(*desc, bo, q, k, v, cs, ga, lse, dvec, dq, s))
       launch_na3d_bwd_any(1, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);
   }
-  if (!launch_na3d_bwd_dkdv_kvp(*desc, bo, q, k, v, cs, ga, lse, dvec, emax, dk, dv, s) &&
+  const bool kvp = launch_na3d_bwd_dkdv_kvp(*desc, bo, q, k, v, cs, ga, lse, dvec, emax, dk, dv, s);
+  if (!kvp) bo.fits = nullptr;
+  if ((!kvp || bo.fits) &&
       !launch_na3d_bwd_dkdv_mfma(*desc, bo, q, k, v, cs, ga, lse, dvec, dk, dv, s) &&
       !launch_na3d_bwd_dkdv_d128(*desc, bo, q, k, v, cs, ga, lse, dvec, dk, dv, s))
     launch_na3d_bwd_any(2, *desc, bo, q, k, v, cs, out, ga, lse, dq, dk, dv, dvec, s);

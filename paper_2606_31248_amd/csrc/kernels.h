@@ -81,6 +81,9 @@ struct BwdOpts {
   int qk_norm = 0;
   float eps = 0.f;
   const void* dout_lo = nullptr;
+  // [B * heads] on the device: the balanced dk/dv pass takes the (batch, head)s where it is not 0, the one-block
+  // pass the others; nullptr: whichever runs takes all
+  const int* fits = nullptr;
 };
 
 // Backward of any problem (float32 arithmetic), one part per call: 0 = D = rowsum(dO * O)
@@ -99,9 +102,12 @@ void launch_na3d_bwd_gate_prep(const strata_na3d_desc& d, const NaOpts& o, const
 
 // The same for bf16 with one logit per (token, head), as a plain backward: da =
 // 2^e dO, lse_f = lse - ln f and D / f into dvec, where sigmoid(g) = f 2^e.
+// With `v` set also fits[B * heads]: 1 where the (batch, head)'s rows of da and v
+// lie inside the float16 ranges of the balanced dk/dv pass, else 0 (row_max: a word
+// per token-head, scratch).
 void launch_na3d_bwd_gate_row_prep(const strata_na3d_desc& d, const NaOpts& o, const void* out, const void* dout,
-                                   const float* lse, float* lse_f, float* dvec, void* da, void* dgate,
-                                   hipStream_t s);
+                                   const float* lse, const void* v, float* lse_f, float* dvec, void* da, void* dgate,
+                                   uint32_t* row_max, int* fits, hipStream_t s);
 
 // bf16 MFMA backward parts; each returns false when the problem has no MFMA variant.
 // dq: query-stationary (the forward's decomposition); dk/dv: key-stationary.

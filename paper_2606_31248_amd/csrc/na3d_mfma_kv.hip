@@ -97,6 +97,7 @@ struct KvArgs {
   int qk_norm;           // QK RMSNorm of the stationary keys and the staged queries
   float eps;
   const uint16_t* dout_lo;  // low term of a two-term dO (with LO)
+  const int* fits;          // (batch, head)s that the balanced kernel took (not 0), or nullptr
 };
 
 // queries whose (border-clamped) window holds position j of an axis of extent L
@@ -156,6 +157,7 @@ __global__ void __launch_bounds__(64 * ZK, (KvCfg<KZ, KY, KX, ZK, NBUF, LO>::WG_
   const int yb = (bid / a.n_xb) % a.n_yb;
   const int zb = (bid / (a.n_xb * a.n_yb)) % a.n_zb;
   const int bh = bid / (a.n_xb * a.n_yb * a.n_zb);
+  if (a.fits && a.fits[bh]) return;
   const int b = bh / a.heads;
   const int H = a.H, W = a.W, Z = a.Z;
   const int y0 = 4 * yb, x0 = 4 * xb, z0 = ZK * zb;
@@ -626,6 +628,7 @@ bool launch_na3d_bwd_dkdv_mfma(const strata_na3d_desc& d, const BwdOpts& o, cons
   a.qk_norm = o.qk_norm;
   a.eps = o.eps;
   a.dout_lo = static_cast<const uint16_t*>(o.dout_lo);
+  a.fits = o.fits;
   // measured on MI355X at 16 tiles x 16 heads x 8x64x64: 3x7x7 is faster with two
   // single-buffered 4-level workgroups per CU (9.8 vs 11.6 ms for the whole
   // backward), 5x9x9 with one double-buffered 8-level workgroup (18.2 vs 18.4 ms)

@@ -94,6 +94,8 @@ struct KvpArgs {
   int ngy, ngx;          // block groups per axis
   float scale, kscale;   // scale, scale * log2(e)
   float eps;             // QK RMSNorm epsilon
+  const int* fits;       // (batch, head)s to take (not 0); nullptr: all
+  int pe;                // P is carried as 2^pe P
 };
 
 
@@ -171,6 +173,7 @@ __global__ void __launch_bounds__(256 * NL, 1) na3d_mfma_kvp_kernel(KvpArgs a) {
   const int gx = bid % a.ngx;
   const int gy = (bid / a.ngx) % a.ngy;
   const int bh = bid / (a.ngx * a.ngy);
+  if (a.fits && !a.fits[bh]) return;
   const int b = bh / a.heads;
   const int H = a.H, W = a.W, Z = a.Z;
   const int npairs = (Z + NL - 1) / NL;  // runs of NL key levels
@@ -188,7 +191,8 @@ __global__ void __launch_bounds__(256 * NL, 1) na3d_mfma_kvp_kernel(KvpArgs a) {
   // scaled alike and dK, dV are scaled back when stored
   const int eb = a.emax[bh];
   const int sh = eb == kEmaxEmpty ? 0 : min(max(eb - 14, -120), 120);
-  const float dsc = __builtin_amdgcn_ldexpf(1.f, -sh), dun = __builtin_amdgcn_ldexpf(1.f, sh);
+  const float dsc = __builtin_amdgcn_ldexpf(1.f, -sh), dun = __builtin_amdgcn_ldexpf(1.f, sh - a.pe);
+  const float pe = (float)a.pe;
 
   // ---- direct-to-LDS copy map: slot s = it*kThreads + tid of the 4 x 4 grid ---
   // square sq = s / 128 (entry (sq / 4, sq % 4) of the axis lists), row
@@ -275,7 +279,7 @@ __global__ void __launch_bounds__(256 * NL, 1) na3d_mfma_kvp_kernel(KvpArgs a) {
       st16(ag, f16_scaled8(ld16(ag), dsc));
     }
     if (soff >= 0) {
-      sl[tid] = -(pl * kLog2e);  // the seed of X: -LSE in log2 units
+      sl[tid] = pe - pl * kLog2e;  // the seed of X: -LSE in log2 units
       sd[tid] = -pd * dsc;
     }
   };
@@ -486,7 +490,7 @@ __global__ void __launch_bounds__(256 * NL, 1) na3d_mfma_kvp_kernel(KvpArgs a) {
         for (int t = 0; t < 4; ++t) accK[t] *= f;
         ex = en;
       }
-      const float sc = __builtin_amdgcn_ldexpf(1.f, 15 - ex);
+      const float sc = __builtin_amdgcn_ldexpf(1.f, 15 - a.pe - ex);
       // P for dV in float16 (bf16's rounding of P alone would put the largest
       // dV of a peaked softmax several percent of RMS(dV) off)
       uint32_t pb[2][2], db[2][2];
@@ -677,6 +681,10 @@ bool launch_na3d_bwd_dkdv_kvp(const strata_na3d_desc& d, const BwdOpts& o, const
   a.scale = d.scale;
   a.kscale = d.scale * kLog2e;
   a.eps = o.eps;
+  a.fits = o.fits;
+  // a key whose weights are all small keeps their bits in float16 down to 2^-28
+  // (weights are at most 1 but for the logits' rounding: 2^14 P has room for 4, dS for 2)
+  a.pe = o.fits ? 14 : 0;
   // two key levels per workgroup (two waves per SIMD, ~240 registers); three
   // levels (three waves per SIMD) leave 168 registers and spill 52 of them:
   // 8.94 against 7.67 ms for the training-tile dK/dV

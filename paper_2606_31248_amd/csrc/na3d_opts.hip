@@ -128,13 +128,32 @@ __global__ void __launch_bounds__(256) gate_prep_kernel(const T* __restrict__ ou
 // P' = f P, so P' (dO'.v - D') = P (a dO.v - D) and P' dO' = P a dO.  No rounded
 // dA is formed: the attention kernels take one bf16 tensor (as without a gate)
 // instead of dA in two terms, which the balanced dK/dV kernel has no room for,
-// and the range of a stays out of P' whatever the gate.  a = 0 gives dO' = 0.
-// Measured with two terms before: the 9x9x9 backward with QK norm, 24 tiles x 16
-// heads x 24x16x16: 9.58 -> 7.26 ms.
+// and the range of a goes into dO' instead of P', whatever the gate.  a = 0 gives
+// dO' = 0.
+// The balanced kernel takes dO' and V in float16 (dO' under one scale per (batch,
+// head)), a narrower range than bf16's, and a shut gate spreads dO' widely; so a
+// pass over dO' and V (0.06 ms of the figure below) tells it which heads fit, and
+// the one-block kernel takes the others.
+// Measured at 24 tiles x 16 heads x 24x16x16, 9x9x9, QK norm, the whole backward:
+// 9.58 ms with dA in two terms, 7.38 ms now (8.21 ms with the one-block kernel alone).
+using half2u = uint16_t __attribute__((ext_vector_type(2)));
+
+// largest magnitude of a row's bf16 values as bits, from its 16-byte pieces in 2^log2_cpr lanes
+__device__ __forceinline__ uint32_t row_max_bits(uint4 x, int log2_cpr) {
+  auto mag = [](uint32_t w) { return __builtin_bit_cast(half2u, w & 0x7FFF7FFFu); };
+  half2u m = __builtin_elementwise_max(__builtin_elementwise_max(mag(x.x), mag(x.y)),
+                                       __builtin_elementwise_max(mag(x.z), mag(x.w)));
+  for (int off = 1 << log2_cpr >> 1; off > 0; off >>= 1)
+    m = __builtin_elementwise_max(m, __builtin_bit_cast(half2u, __shfl_xor(__builtin_bit_cast(uint32_t, m), off)));
+  return max(m.x, m.y);
+}
+
 __global__ void __launch_bounds__(256) gate_row_prep_kernel(const uint16_t* __restrict__ out,
                                                             const uint16_t* __restrict__ dout,
                                                             const uint16_t* __restrict__ gate,
-                                                            const float* __restrict__ lse, float* __restrict__ lse_f,
+                                                            const float* __restrict__ lse,
+                                                            const uint16_t* __restrict__ v, uint32_t* __restrict__ row_max,
+                                                            float* __restrict__ lse_f,
                                                             float* __restrict__ dvec, uint16_t* __restrict__ da,
                                                             uint16_t* __restrict__ dgate, int64_t n, int log2_cpr) {
   using PC = Piece<uint16_t>;
@@ -168,7 +187,65 @@ __global__ void __launch_bounds__(256) gate_row_prep_kernel(const uint16_t* __re
   }
 #pragma unroll
   for (int e = 0; e < E; ++e) g[e] *= mul;
-  *reinterpret_cast<uint4*>(da + gid * E) = PC::pack(g);
+  const uint4 packed = PC::pack(g);
+  *reinterpret_cast<uint4*>(da + gid * E) = packed;
+  if (v) {
+    const uint32_t mo = row_max_bits(packed, log2_cpr);
+    const uint32_t mv = row_max_bits(*reinterpret_cast<const uint4*>(v + gid * E), log2_cpr);
+    if ((gid & ((1 << log2_cpr) - 1)) == 0) row_max[row] = mo | mv << 16;
+  }
+}
+
+// Whether a (batch, head) fits the balanced kernel's float16 operands, from its
+// rows' largest magnitudes (one workgroup per (batch, head)); a row of zeros always
+// does.
+//   V: below 2^16 (the largest bf16 value there is 65280), and every row's largest
+//     value at least 2^-10, so that float16's spacing of 2^-24 is 2^-14 of it;
+//   dO': finite, and every row's largest value within 2^24 of the head's, which is
+//     staged between 2^13 and 2^14: half of 2^-24 is 2^-14 of it or less.
+// 2^-14 is a quarter of the rounding of dS, and less than P had in bf16.
+constexpr int kFitsThreads = 1024;
+__global__ void __launch_bounds__(kFitsThreads) gate_fits_kernel(const uint32_t* __restrict__ row_max,
+                                                                 int* __restrict__ fits, int64_t n) {
+  const uint32_t* w = row_max + blockIdx.x * n;
+  uint32_t omax = 0, omin = 0xFFFFu, vmax = 0, vmin = 0xFFFFu;
+  for (int64_t i0 = threadIdx.x; i0 < n; i0 += 8 * kFitsThreads) {
+    uint32_t x[8];  // loads in flight together: a head's rows are read by one workgroup
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = w[min(i0 + t * kFitsThreads, n - 1)];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const uint32_t o = x[t] & 0xFFFFu, v = x[t] >> 16;
+      omax = max(omax, o);
+      vmax = max(vmax, v);
+      omin = o ? min(omin, o) : omin;
+      vmin = v ? min(vmin, v) : vmin;
+    }
+  }
+  constexpr int kWaves = kFitsThreads / 64;
+  __shared__ uint32_t part[kWaves][4];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    omax = max(omax, (uint32_t)__shfl_xor((int)omax, off));
+    omin = min(omin, (uint32_t)__shfl_xor((int)omin, off));
+    vmax = max(vmax, (uint32_t)__shfl_xor((int)vmax, off));
+    vmin = min(vmin, (uint32_t)__shfl_xor((int)vmin, off));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    uint32_t* p = part[threadIdx.x >> 6];
+    p[0] = omax; p[1] = omin; p[2] = vmax; p[3] = vmin;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int t = 1; t < kWaves; ++t) {
+    omax = max(omax, part[t][0]);
+    omin = min(omin, part[t][1]);
+    vmax = max(vmax, part[t][2]);
+    vmin = min(vmin, part[t][3]);
+  }
+  constexpr uint32_t kInf = 0x7F80u, k2p16 = (127u + 16u) << 7, k2m10 = (127u - 10u) << 7;
+  fits[blockIdx.x] = omax < kInf && (omin >> 7) + 24 >= omax >> 7 && vmax < k2p16 && vmin >= k2m10;
 }
 
 int64_t rows(const strata_na3d_desc& d) { return (int64_t)d.B * d.heads * d.Z * d.H * d.W; }
@@ -208,14 +285,17 @@ void launch_na3d_bwd_gate_prep(const strata_na3d_desc& d, const NaOpts& o, const
 }
 
 void launch_na3d_bwd_gate_row_prep(const strata_na3d_desc& d, const NaOpts& o, const void* out, const void* dout,
-                                   const float* lse, float* lse_f, float* dvec, void* da, void* dgate,
-                                   hipStream_t s) {
+                                   const float* lse, const void* v, float* lse_f, float* dvec, void* da, void* dgate,
+                                   uint32_t* row_max, int* fits, hipStream_t s) {
   const int64_t n = rows(d);
   const int l2 = d.head_dim == 32 ? 2 : d.head_dim == 64 ? 3 : 4;  // 16-byte pieces per row
   hipLaunchKernelGGL(gate_row_prep_kernel, dim3((unsigned)(((n << l2) + 255) / 256)), dim3(256), 0, s,
                      static_cast<const uint16_t*>(out), static_cast<const uint16_t*>(dout),
-                     static_cast<const uint16_t*>(o.gate), lse, lse_f, dvec, static_cast<uint16_t*>(da),
-                     static_cast<uint16_t*>(dgate), n, l2);
+                     static_cast<const uint16_t*>(o.gate), lse, static_cast<const uint16_t*>(v), row_max, lse_f, dvec,
+                     static_cast<uint16_t*>(da), static_cast<uint16_t*>(dgate), n, l2);
+  if (v)
+    hipLaunchKernelGGL(gate_fits_kernel, dim3((unsigned)(d.B * d.heads)), dim3(kFitsThreads), 0, s, row_max, fits,
+                       (int64_t)d.Z * d.H * d.W);
 }
 
 }  // namespace strata

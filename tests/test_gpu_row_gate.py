@@ -66,3 +66,54 @@ def test_backward_over_the_sigmoid_range(shape, window, qk_norm):
             assert not got[rows].any()
             continue
         check_close(got[rows], refs[0][rows], "bf16", f"dq at logit {logit}")
+
+
+def fits_flags(ws, shape):
+    """The words of the workspace that say which (batch, head)s the balanced dK/dV pass took: they follow lse' and a
+    word per row where the second term of dA would be (behind D, the dO exponents and the first term)."""
+    b, h, z, y, x, d = shape
+    n = b * h * z * y * x
+    al = lambda m: (m + 255) // 256 * 256
+    at = al(4 * n) + al(4 * b * h) + al(2 * d * n) + 8 * n
+    return ws[at:at + 4 * b * h].view(torch.int32).cpu().numpy().reshape(b, h)
+
+
+# 56 heads, four workgroups to each: the balanced pass fills the chip
+@pytest.mark.parametrize("shape,window,kinds", [((1, 56, 5, 9, 16, 64), (5, 9, 9), 4), ((1, 56, 9, 9, 16, 64), (9, 9, 9), 2)])
+def test_ranges_that_float16_does_not_hold(shape, window, kinds):
+    """Heads by turns: ordinary; a gate open at x < 3, a = 2e-9 up to x = 7 and 1e-17 beyond (all that the keys of the
+    last columns are seen by); V of 1e5; V of 1e-7 from x = 4 on.  Every four columns are held to the bf16 rule by
+    themselves."""
+    b, h, z, y, x, d = shape
+    few = (b, kinds) + shape[2:]
+    q, k, v, dout = (I.gaussian(few, 73, s, "bf16") for s in (0, 1, 2, I.STREAM_DO))
+    g = I.rng(73, I.STREAM_GATE).normal(0.0, 2.0, few[:-1]).astype(np.float32)
+    g[:, 1] = np.where(np.arange(x) < 3, 2.0, np.where(np.arange(x) < 8, -20.0, -39.0))
+    g = I.f32_to_bf16_bits(g)
+    mult = np.ones(few[:-1], np.float32)
+    if kinds > 2:
+        mult[:, 2] = 1e5
+        mult[:, 3] = np.where(np.arange(x) < 4, 1.0, 1e-7)
+    v = I.f32_to_bf16_bits(oracle.widen(v, "bf16").astype(np.float32) * mult[..., None])
+    scale = d ** -0.5
+    wide = [oracle.widen(a, "bf16") for a in (q, k, v, dout, g)]
+    # out and lse from the oracle: the 5x9x9 forward's V has float16's range
+    ro, rl = oracle.na3d_fwd(*wide[:3], window, scale, qk_norm=True, gate=wide[4])
+    refs = oracle.na3d_bwd(*wide[:4], window, scale, qk_norm=True, gate=wide[4])
+    every = lambda a, dtype="bf16": dev_tensor(np.concatenate([a] * (h // kinds), 1), dtype)
+    qd, kd, vd, dod, gd = (every(a) for a in (q, k, v, dout, g))
+    out, lse = every(I.f32_to_bf16_bits(ro.astype(np.float32))), every(rl, "f32")
+    desc, opts = B.desc_for(qd, window, scale), B.make_opts(True, 1e-6, gd)
+    ws = torch.empty(B.strata_na3d_bwd_ex_workspace_size(desc, opts), dtype=torch.uint8, device="cuda")
+    dq, dk, dv, dg = torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(gd)
+    B.strata_na3d_bwd_ex(desc, opts, qd, kd, vd, None, out, dod, lse, dq, dk, dv, dg, ws)
+    for name, t, ref in zip(("dq", "dk", "dv"), (dq, dk, dv), refs):
+        for i in range(kinds, h, kinds):
+            assert torch.equal(t[:, :kinds], t[:, i:i + kinds])
+        got = host_f64(t[:, :kinds])
+        for i in range(kinds):
+            for x0 in range(0, x, 4):
+                cut = np.s_[:, i, :, :, x0:x0 + 4]
+                check_close(got[cut], ref[cut], "bf16", f"{name}, head {i}, columns from {x0}")
+    # the balanced pass took the ordinary heads alone
+    assert np.array_equal(fits_flags(ws, shape), [[1, 0, 0, 0][:kinds] * (h // kinds)])
