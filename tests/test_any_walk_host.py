@@ -148,3 +148,21 @@ def test_any_walk(tmp_path):
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout + out.stderr
     assert out.stdout.startswith("ok")
+
+
+def test_waves_per_tile_of_the_gpu_shapes(tmp_path):
+    """The number of waves that share a tile at each shape of the any-window GPU test is the one written there."""
+    from test_gpu_any_window import SHAPES
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    assert {s[3] for s in SHAPES} == {1, 2, 4}
+    src = tmp_path / "waves.cpp"
+    exe = tmp_path / "waves"
+    calls = "\n".join('printf("%d ", any_dims({}, 1.f, 0, 0.f).split);'.format(", ".join(map(str, s[0][:5] + s[1])))
+                      for s in SHAPES)
+    src.write_text(HARNESS[:HARNESS.index("int main()")] + "int main() {\n" + calls + "\nreturn 0;\n}\n")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-Wno-unused-function", "-Wno-unknown-pragmas", "-I", CSRC, str(src), "-o", str(exe)],
+                   check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and [int(x) for x in out.stdout.split()] == [s[3] for s in SHAPES]
