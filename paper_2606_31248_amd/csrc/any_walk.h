@@ -219,13 +219,17 @@ __host__ __device__ __forceinline__ uint32_t xcd_order(uint32_t i, uint32_t n) {
   return x * q + min(x, r) + i / 8;
 }
 
+// Positions of an axis that a tile's box spans, at most: the queries that see keys
+// i .. i + 15 are those from 0 on where i < k and those up to L - 1 where i + 15 >=
+// L - k, so all of them on an axis of up to 2 k + 14.
+inline int64_t box_most(int64_t L, int64_t k) { return L < 16 + 2 * k ? L : 16 + 2 * k; }
+
 // Whether the 32-bit token and block indices above hold: every problem that a
 // device can hold (2^32 tokens of the narrowest rows are 256 GiB a tensor) and
 // whose windows can be walked in a lifetime.
 inline bool any_fits(int B, int heads, int Z, int H, int W, int kz, int ky, int kx) {
-  // a box spans at most 16 + 1.5 k positions of an axis (the queries that see keys near a border)
-  auto most = [](int L, int k) { return (double)(L < 16 + k + k / 2 ? L : 16 + k + k / 2); };
-  return (double)B * heads * Z * H * W < 4294967296.0 && most(Z, kz) * most(H, ky) * most(W, kx) < 1073741824.0 &&
+  return (double)B * heads * Z * H * W < 4294967296.0 &&
+         (double)box_most(Z, kz) * (double)box_most(H, ky) * (double)box_most(W, kx) < 1073741824.0 &&
          any_blocks(any_dims(B, heads, Z, H, W, kz, ky, kx, 1.f, 0, 0.f)) < ((int64_t)1 << 30);
 }
 

@@ -106,6 +106,19 @@ int main() {
     for (uint32_t i : {0u, n - 1, n, (uint32_t)(rng() >> 2), q * n - 1, q * n, (1u << 30) - 1})
       if (i < (1u << 30) && f.div(i) != i / n) return printf("%u / %u = %u\n", i, n, f.div(i)), 1;
   }
+  // a tile's box along an axis, at every length up to 100 with every window: inside the axis, at most box_most long
+  for (int L = 1; L <= 100; ++L)
+    for (int k = 1; k <= L; ++k) {
+      if (k % 2 == 0 && k < L) continue;
+      for (int lb = 0; lb <= 4; ++lb)
+        for (int t = 0; t << lb < L; ++t)
+          for (int inv = 0; inv < 2; ++inv) {
+            int pos, o, l, c;
+            bool in = true;
+            const int n = inv ? Walk::axis<true>(t, lb, L, k, 0, pos, in, o, l, c) : Walk::axis<false>(t, lb, L, k, 0, pos, in, o, l, c);
+            if (o < 0 || o + n > L || n > box_most(L, k)) return printf("box of %d of %d, window %d\n", n, L, k), 1;
+          }
+    }
   for (int bh = 1; bh < 400; ++bh) {  // every grid has a wave, few waves have none
     const AnyDims d = any_dims(1, bh, 5, 9, 9, 3, 3, 3, 1.f, 0, 0.f);
     const int per = 4 / d.split, groups = (bh + per - 1) / per;
