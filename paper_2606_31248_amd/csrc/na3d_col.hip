@@ -272,10 +272,12 @@ bool launch_na3d_fwd_col(const strata_na3d_desc& d, const NaOpts& o, const void*
 //   one per channel (CHAN): dA = a dO as two bf16 terms, formed in registers.
 // What bounds it: HBM (8 rows of 128 bytes read or written per token), as long as
 // enough waves are resident: 9.3 KB of LDS and at most 168 registers per wave keep
-// three per SIMD.  Measured at 24 tiles x 16 heads x 24x16x16, window 24x1x1, QK
-// norm and a gate logit per token: 0.57 ms (4.3 TB/s; a large copy on the card
-// reaches 5.0), against 0.65 ms behind a 0.15 ms pass that formed D and the
-// gate's part, with one wave per SIMD or two.
+// three per SIMD (more with Z <= 16).  Two blocks of levels with a gate per channel
+// stage a third tile (14 KB) and have two.  Measured at 24 tiles x 16 heads x
+// 24x16x16, window 24x1x1, QK norm and a gate logit per token: 0.50 ms (4.9 TB/s,
+// the rate of a large copy on the card), against 0.65 ms behind a 0.15 ms pass that
+// formed D and the gate's part, with one wave per SIMD or two.  (That variant, at
+// 168 registers, keeps one of them in scratch.)
 struct ColBwdArgs {
   const uint16_t* q;
   const uint16_t* k;

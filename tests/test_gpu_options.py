@@ -121,8 +121,8 @@ FWD_SHAPES = [
     ((1, 11, 8, 16, 24, 64), (3, 7, 7), "bf16"),  # level-sweep kernel, ragged head group
     ((2, 3, 5, 19, 21, 64), (3, 7, 7), "bf16"),   # query-stationary MFMA kernel
     ((1, 2, 6, 24, 24, 64), (5, 9, 9), "bf16"),   # query-stationary MFMA kernel, 5x9x9
-    ((2, 2, 3, 16, 12, 32), (3, 5, 7), "bf16"),   # plain kernel, bf16
-    ((1, 2, 4, 9, 11, 32), (3, 5, 7), "f32"),     # plain kernel, float32
+    ((2, 2, 3, 16, 12, 32), (3, 5, 7), "bf16"),   # any-window kernel, bf16
+    ((1, 2, 4, 9, 11, 32), (3, 5, 7), "f32"),     # any-window kernel, float32
     ((1, 1, 3, 8, 8, 64), (3, 3, 3), "f32"),
 ]
 

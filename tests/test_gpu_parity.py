@@ -124,12 +124,12 @@ def test_fwd_tiny_f32_full():
 
 
 @pytest.mark.parametrize("shape,window", [
-    ((1, 2, 9, 10, 11, 64), (9, 9, 9)),   # 729 keys: every lane of a query's wave takes 11-12
-    ((2, 1, 3, 5, 6, 32), (1, 3, 5)),     # 15 keys: most lanes of the wave take none
+    ((1, 2, 9, 10, 11, 64), (9, 9, 9)),   # 729 keys
+    ((2, 1, 3, 5, 6, 32), (1, 3, 5)),     # 15 keys: most of a tile's waves take no chunk
 ])
-def test_fwd_f32_one_wave_per_query(shape, window):
-    """Small float32 problems run one wave per query (the lanes split the window's
-    keys and merge their softmax states): full grids against the oracle."""
+def test_fwd_f32_small_grids(shape, window):
+    """Small float32 problems run four waves to a tile of queries (they split the box's
+    chunks and merge their softmax states): full grids against the oracle."""
     pl = I.random_placement(shape[0], shape[3], shape[4], 95)
     c32 = oracle_coords(pl, shape[3], shape[4])
     (q, k, v), out, lse, scale = run_fwd(shape, window, "f32", 47, c32)

@@ -79,8 +79,8 @@ def fits_flags(ws, shape):
 
 
 # 56 heads, four workgroups to each: the balanced pass fills the chip
-@pytest.mark.parametrize("shape,window,kinds", [((1, 56, 5, 9, 16, 64), (5, 9, 9), 4), ((1, 56, 9, 9, 16, 64), (9, 9, 9), 2)])
-def test_ranges_that_float16_does_not_hold(shape, window, kinds):
+@pytest.mark.parametrize("shape,window,kinds,norm", [((1, 56, 5, 9, 16, 64), (5, 9, 9), 4, True), ((1, 56, 9, 9, 16, 64), (9, 9, 9), 2, False)])
+def test_ranges_that_float16_does_not_hold(shape, window, kinds, norm):
     """Heads by turns: ordinary; a gate open at x < 3, a = 2e-9 up to x = 7 and 1e-17 beyond (all that the keys of the
     last columns are seen by); V of 1e5; V of 1e-7 from x = 4 on.  Every four columns are held to the bf16 rule by
     themselves."""
@@ -98,15 +98,17 @@ def test_ranges_that_float16_does_not_hold(shape, window, kinds):
     scale = d ** -0.5
     wide = [oracle.widen(a, "bf16") for a in (q, k, v, dout, g)]
     # out and lse from the oracle: the 5x9x9 forward's V has float16's range
-    ro, rl = oracle.na3d_fwd(*wide[:3], window, scale, qk_norm=True, gate=wide[4])
-    refs = oracle.na3d_bwd(*wide[:4], window, scale, qk_norm=True, gate=wide[4])
+    c32 = None if norm else coords_for(few, 104)
+    ro, rl = oracle.na3d_fwd(*wide[:3], window, scale, coords=c32, qk_norm=norm, gate=wide[4])
+    refs = oracle.na3d_bwd(*wide[:4], window, scale, coords=c32, qk_norm=norm, gate=wide[4])
     every = lambda a, dtype="bf16": dev_tensor(np.concatenate([a] * (h // kinds), 1), dtype)
     qd, kd, vd, dod, gd = (every(a) for a in (q, k, v, dout, g))
     out, lse = every(I.f32_to_bf16_bits(ro.astype(np.float32))), every(rl, "f32")
-    desc, opts = B.desc_for(qd, window, scale), B.make_opts(True, 1e-6, gd)
+    desc, opts = B.desc_for(qd, window, scale), B.make_opts(norm, 1e-6, gd)
+    cs = None if norm else gpu_phases(c32, d)
     ws = torch.empty(B.strata_na3d_bwd_ex_workspace_size(desc, opts), dtype=torch.uint8, device="cuda")
     dq, dk, dv, dg = torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(qd), torch.empty_like(gd)
-    B.strata_na3d_bwd_ex(desc, opts, qd, kd, vd, None, out, dod, lse, dq, dk, dv, dg, ws)
+    B.strata_na3d_bwd_ex(desc, opts, qd, kd, vd, cs, out, dod, lse, dq, dk, dv, dg, ws)
     for name, t, ref in zip(("dq", "dk", "dv"), (dq, dk, dv), refs):
         for i in range(kinds, h, kinds):
             assert torch.equal(t[:, :kinds], t[:, i:i + kinds])
