@@ -238,7 +238,9 @@ strata_status strata_na3d_fwd_ex(const strata_na3d_desc* desc, const strata_na3d
  * V keeps bf16's range: with one logit per token-head at 5x9x9 and 9x9x9 a (batch,
  * head) takes the balanced dK/dV kernel only where 2^e dO spans less than 2^24 from
  * row to row and V's rows lie between 2^-10 and 2^16 (their largest magnitudes),
- * and the one-block kernel otherwise, as does a problem too small to fill the chip.
+ * and the one-block kernel otherwise, as does a problem too small to fill the chip;
+ * the balanced kernel's weights P (times 2^14, float16) keep their bits down to
+ * 2^-28 and are 0 below 2^-39.
  * The norm is applied inside the attention kernels.  The library allocates
  * nothing. */
 size_t strata_na3d_bwd_ex_workspace_size(const strata_na3d_desc* desc,
